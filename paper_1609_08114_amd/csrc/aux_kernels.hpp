@@ -126,6 +126,12 @@ hipError_t launch_lane(const KParams& P, int grid, hipStream_t s);
 template <int R, int C, int NWV, int WPE>
 const void* kernel_ptr_lane();
 
+// Streaming kernel with pending pivots (simplex_pend.hip): LPs of
+// pend_shape(), P.ws_lds doubles of dynamic LDS for the pending factors.
+hipError_t launch_pend(const KParams& P, int grid, size_t lds_bytes, hipStream_t s);
+const void* pend_kernel_ptr();
+int pend_threads();
+
 // Streaming kernel (simplex_gm.hip).
 // deep: the launch's bin is known not to be empty: for tableaux of up to 512
 // rows, more loads in flight per lane and on-chip columns in the dynamic LDS

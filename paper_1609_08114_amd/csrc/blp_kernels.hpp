@@ -63,6 +63,7 @@ struct KParams {
     int32_t ws_ld;   // leading dimension (rows, multiple of 16)
     int32_t ws_cols; // columns available per slot
     int32_t ws_lds;  // doubles of dynamic LDS for on-chip columns (0: none)
+    int32_t skip_pend;  // streaming kernel: 1 leaves the LPs of pend_shape() to simplex_pend_kernel
     // pivot trace of the 112 x 112 block tile: LP k's record at
     // trace + k * trace_stride is [count, row 0, slot 0, row 1, slot 1, ...]
     int32_t* trace;
@@ -76,6 +77,13 @@ struct KParams {
     int32_t layout;
     uint64_t seed;
 };
+
+// LPs that the streaming kernel with pending pivots takes (simplex_pend.hip:
+// one row and two column slots per thread of 512, whatever the number of
+// artificial rows); the others stay with the one that streams the tableau at
+// every pivot.
+constexpr int kPendRows = 512, kPendSlots = 1024;
+__host__ __device__ inline bool pend_shape(int m, int n) { return m <= kPendRows && n + m <= kPendSlots; }
 
 // Workgroup barrier for communication through LDS only: each wave waits for
 // its own LDS operations, not for its global loads and stores, so output

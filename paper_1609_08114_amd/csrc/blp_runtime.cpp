@@ -124,7 +124,7 @@ struct blp_handle_s {
     int nreg = 0;
     void* scratch = nullptr;  // this device's copy of the static scratch (allocation-free entry point)
     std::vector<int> reg_workers;  // persistent grid per variant
-    int gm_occ = 1;
+    size_t pend_static = 0;        // static LDS of the pending-pivot streaming kernel, bytes
     int direct_v = -1;  // the last solve's one-launch variant (no binning), or -1
     // device buffers
     DevBuf meta;     // m, n, kind (int32) + a_off, row_off, col_off (int64) for non-uniform batches
@@ -353,6 +353,14 @@ blp_error blp_create(blp_handle* out, const blp_options* opt) {
         if (o.workers_per_cu > 0) occ = std::min(occ, (int)o.workers_per_cu);
         h->reg_workers.push_back(occ * h->cu_count);
     }
+    hipFuncAttributes pa{};
+    if (hipFuncGetAttributes(&pa, pend_kernel_ptr()) != hipSuccess ||
+        hipFuncSetAttribute(pend_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)(h->lds_per_block - pa.sharedSizeBytes)) != hipSuccess) {
+        delete h;
+        return BLP_ERR_HIP;
+    }
+    h->pend_static = pa.sharedSizeBytes;
 #ifdef BLP_PHASE_TIMERS
     if (hipMalloc(&h->timers, TM_SLOTS * sizeof(unsigned long long)) == hipSuccess)
         (void)hipMemset(h->timers, 0, TM_SLOTS * sizeof(unsigned long long));
@@ -478,6 +486,19 @@ static void gm_lds_plan(blp_handle h, int ld, int cols, bool deep, bool shared, 
     *tab = (int32_t)t;
 }
 
+// Workgroups per CU of the pending-pivot streaming kernel and the dynamic LDS
+// of each (its pending factors; more pivots fit the larger share).  Two per CU
+// hide each other's memory latency; a batch that leaves CUs with one LP at
+// most gets the whole CU's LDS for it.
+static int pend_plan(blp_handle h, int64_t lps, size_t* bytes) {
+    int occ = lps > h->cu_count ? 2 : 1;
+    if (h->opt.workers_per_cu > 0) occ = std::min(occ, (int)h->opt.workers_per_cu);
+    // (LDS is handed out in units of at most 2 KiB)
+    const size_t share = std::min(h->lds_per_cu / (size_t)occ, h->lds_per_block) & ~(size_t)2047;
+    *bytes = share - h->pend_static;
+    return occ;
+}
+
 // Everything one solve needs after validation.
 struct SolvePlan {
     KParams P{};
@@ -485,6 +506,9 @@ struct SolvePlan {
     int64_t n_box = 0;
     int gm_ld = 0, gm_cols = 0, gm_workers = 0;
     bool gm_deep = false;  // the streaming kernel's deep instantiation (deep loads, on-chip columns)
+    int64_t n_pend = 0, n_gm = 0;  // LPs that may reach each streaming kernel
+    int pend_workers = 0;
+    size_t pend_lds = 0;
     bool gm_shared = false;  // register kernels may run beside it (keep LDS for them)
     size_t gm_lds = 0;
     std::vector<char> maybe;  // register variants that can receive LPs
@@ -557,6 +581,8 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
     in.remap_streams = remap_streams;
     in.lpc = h->opt.pivot_rule == BLP_RULE_LPC;
     in.stream_all = stream_all;
+    // (the row-major workspace is the layout comparison's, at one pivot a time)
+    if (h->opt.layout == BLP_LAYOUT_COLUMN) in.pend = &pend_shape;
     Plan& pl = h->plan;
     if (plan_batch(in, pl) != PLAN_OK) return fail(h, (blp_error)pl.code, "%s", pl.msg.c_str());
     const bool any_simplex = pl.any_simplex, any_box = pl.any_box;
@@ -729,11 +755,22 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         sp.gm_cols = max_cols;
         int occ = 1;
         sp.gm_shared = std::find(sp.maybe.begin(), sp.maybe.end(), (char)1) != sp.maybe.end();
-        gm_lds_plan(h, sp.gm_ld, sp.gm_cols, sp.gm_deep, sp.gm_shared, &sp.gm_lds, &P.ws_lds, &occ);
-        if (h->opt.workers_per_cu > 0) occ = std::min(occ, (int)h->opt.workers_per_cu);
+        sp.n_pend = pl.n_may_pend;
+        sp.n_gm = n_may_stream - pl.n_may_pend;
+        if (sp.n_gm > 0 || stream_all) {
+            gm_lds_plan(h, sp.gm_ld, sp.gm_cols, sp.gm_deep, sp.gm_shared, &sp.gm_lds, &P.ws_lds, &occ);
+            if (h->opt.workers_per_cu > 0) occ = std::min(occ, (int)h->opt.workers_per_cu);
+        }
         // one workspace slot per streaming workgroup, no more workgroups
-        // than LPs that can reach the streaming kernel
-        sp.gm_workers = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * h->cu_count, n_may_stream));
+        // than LPs that can reach the streaming kernel (the two streaming
+        // kernels run one after the other and share the slots)
+        sp.gm_workers = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * h->cu_count,
+                                                                    stream_all ? n_may_stream : sp.n_gm));
+        if (sp.n_pend > 0) {
+            const int64_t w = (int64_t)pend_plan(h, sp.n_pend, &sp.pend_lds) * h->cu_count;
+            sp.pend_workers = (int)std::min<int64_t>(w, sp.n_pend);
+        }
+        int slots = std::max(sp.gm_workers, sp.pend_workers);
         const size_t slot = (size_t)max_slot;
         if (arena) {
             // as many workspace slots as the scratch still holds (fewer
@@ -743,12 +780,14 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
                 return fail(h, BLP_ERR_TOO_LARGE,
                             "static scratch of %zu bytes cannot hold one streaming workspace slot of %zu bytes",
                             arena->cap, sizeof(double) * slot);
-            sp.gm_workers = (int)std::min<int64_t>(sp.gm_workers, fit);
+            slots = (int)std::min<int64_t>(slots, fit);
         }
         if (ws_budget > 0)
-            sp.gm_workers = (int)std::max<int64_t>(
-                1, std::min<int64_t>(sp.gm_workers, (int64_t)(ws_budget / (sizeof(double) * slot))));
-        BUF_TRY(h, arena, h->ws, sizeof(double) * slot * (size_t)sp.gm_workers, P.ws);
+            slots =
+                (int)std::max<int64_t>(1, std::min<int64_t>(slots, (int64_t)(ws_budget / (sizeof(double) * slot))));
+        sp.gm_workers = std::min(sp.gm_workers, slots);
+        sp.pend_workers = std::min(sp.pend_workers, slots);
+        BUF_TRY(h, arena, h->ws, sizeof(double) * slot * (size_t)slots, P.ws);
         P.ws_slot = (int64_t)slot;
         P.ws_ld = sp.gm_ld;
         P.ws_cols = sp.gm_cols;
@@ -791,6 +830,25 @@ static blp_error enqueue_binning(blp_handle h, SolvePlan& sp, hipStream_t s) {
         HIP_TRY(h, launch_order_bins(sp.P, nbins, bin_count, sp.P.bin_off, sp.list, sp.olist, s));
     HIP_TRY(h, h->mark(nbins, false, s));
     return BLP_SUCCESS;
+}
+
+// The streaming bin's launches: each of the two streaming kernels that LPs of
+// the batch may need takes its own from the same list (a persistent launch of
+// the second counts on a head of its own: the one of the hyperbox bin, which
+// that bin's kernel does not use).  `grid` workgroups at most.
+static hipError_t launch_streaming(const SolvePlan& sp, const KParams& P, int64_t grid, hipStream_t s) {
+    const bool both = sp.n_pend > 0 && sp.n_gm > 0;
+    if (sp.n_pend > 0) {
+        KParams Q = P;
+        Q.ws_lds = (int32_t)(sp.pend_lds / sizeof(double));
+        const hipError_t e =
+            launch_pend(Q, (int)std::min<int64_t>(P.direct ? grid : sp.pend_workers, grid), sp.pend_lds, s);
+        if (e != hipSuccess || !both) return e;
+    }
+    KParams Q = P;
+    Q.skip_pend = both ? 1 : 0;
+    if (both) Q.bin_head += kHeadStride;
+    return launch_gm(Q, (int)std::min<int64_t>(P.direct ? grid : sp.gm_workers, grid), sp.gm_lds, s, sp.gm_deep);
 }
 
 // One persistent launch per kernel class that can receive LPs.  For a mixed
@@ -837,7 +895,7 @@ static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, 
         if (err == hipSuccess) {
             what = "kernel launch";
             err = v < nreg ? h->variants[v].launch(Q, reg_grid(h, v, K), st)
-                           : launch_gm(Q, (int)std::min<int64_t>(sp.gm_workers, K), sp.gm_lds, st, sp.gm_deep);
+                           : launch_streaming(sp, Q, K, st);
         }
         if (err == hipSuccess) {
             what = "event record";
@@ -884,7 +942,9 @@ static blp_error enqueue_baseline(blp_handle h, SolvePlan& sp, hipStream_t s) {
         if (nv == 0) continue;
         KParams Q = P;
         Q.bin = v;
-        const int64_t chunk = v == nreg ? sp.gm_workers : (mode == BLP_MODE_GRID ? nv : 1);
+        const int stream_slots = sp.n_gm == 0 ? sp.pend_workers
+                                 : sp.n_pend == 0 ? sp.gm_workers : std::min(sp.gm_workers, sp.pend_workers);
+        const int64_t chunk = v == nreg ? stream_slots : (mode == BLP_MODE_GRID ? nv : 1);
         const int64_t per = v < nreg ? h->variants[v].lps_per_block : 1;  // LPs per workgroup
         HIP_TRY(h, h->mark(v, true, s));
         for (int64_t first = 0; first < nv; first += chunk) {
@@ -893,11 +953,11 @@ static blp_error enqueue_baseline(blp_handle h, SolvePlan& sp, hipStream_t s) {
             const int grid = (int)((std::min<int64_t>(chunk, nv - first) + per - 1) / per);
             if (v == nreg) {
                 if (mode == BLP_MODE_GRID) {
-                    HIP_TRY(h, launch_gm(Q, grid, sp.gm_lds, s, sp.gm_deep));
+                    HIP_TRY(h, launch_streaming(sp, Q, grid, s));
                 } else {
                     for (int64_t q = first; q < first + grid; ++q) {
                         Q.direct_first = q;
-                        HIP_TRY(h, launch_gm(Q, 1, sp.gm_lds, s, sp.gm_deep));
+                        HIP_TRY(h, launch_streaming(sp, Q, 1, s));
                     }
                 }
             } else {
@@ -921,7 +981,8 @@ static std::vector<uint64_t> graph_signature(blp_handle h, const SolvePlan& sp, 
                                (uint64_t)(uintptr_t)P.y, (uint64_t)(uintptr_t)P.list, (uint64_t)(uintptr_t)P.bin_len,
                                (uint64_t)(uintptr_t)P.ws, (uint64_t)P.ws_slot, (uint64_t)P.ws_ld,
                                (uint64_t)P.ws_cols, (uint64_t)(uintptr_t)P.m, (uint64_t)(uintptr_t)sp.binid,
-                               (uint64_t)sp.gm_lds, (uint64_t)sp.gm_workers, (uint64_t)sp.gm_deep};
+                               (uint64_t)sp.gm_lds, (uint64_t)sp.gm_workers, (uint64_t)sp.gm_deep, (uint64_t)sp.n_pend,
+                               (uint64_t)sp.n_gm, (uint64_t)sp.pend_workers, (uint64_t)sp.pend_lds};
     for (int v = 0; v < h->nreg; ++v) g.push_back((uint64_t)sp.maybe[v] | ((uint64_t)h->remap[v] << 8));
     g.push_back((uint64_t)(int64_t)sp.direct_v);
     g.push_back((uint64_t)P.pivot_rule);
@@ -1450,11 +1511,16 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
         Q.bin = nreg;
         Q.shared_in = 1;
         const int ld = ((m + 2 + 15) / 16) * 16, gcols = n + m + 1;
-        const bool deep = true;
+        const bool deep = true, pend = h->opt.layout == BLP_LAYOUT_COLUMN && pend_shape(m, n);
         int occ = 1;
         size_t lds = 0;
-        gm_lds_plan(h, ld, gcols, deep, false, &lds, &Q.ws_lds, &occ);
-        if (h->opt.workers_per_cu > 0) occ = std::min(occ, (int)h->opt.workers_per_cu);
+        if (pend) {
+            occ = pend_plan(h, count, &lds);
+            Q.ws_lds = (int32_t)(lds / sizeof(double));
+        } else {
+            gm_lds_plan(h, ld, gcols, deep, false, &lds, &Q.ws_lds, &occ);
+            if (h->opt.workers_per_cu > 0) occ = std::min(occ, (int)h->opt.workers_per_cu);
+        }
         const int64_t workers = std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * h->cu_count, count));
         const size_t slot = (size_t)ld * gcols;
         HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * slot * (size_t)workers));
@@ -1462,7 +1528,7 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
         Q.ws_slot = (int64_t)slot;
         Q.ws_ld = ld;
         Q.ws_cols = gcols;
-        HIP_TRY(h, launch_gm(Q, (int)workers, lds, s, deep));
+        HIP_TRY(h, pend ? launch_pend(Q, (int)workers, lds, s) : launch_gm(Q, (int)workers, lds, s, deep));
     }
     HIP_TRY(h, end_call(h, s));
     return BLP_SUCCESS;
@@ -1853,7 +1919,10 @@ blp_error blp_autotune(blp_handle h, const blp_batch* B, int32_t sample, const c
                 if (w < nreg) {
                     HIP_TRY(h, h->variants[w].launch(Q, reg_grid(h, w, S), s));
                 } else {
-                    HIP_TRY(h, launch_gm(Q, (int)std::min<int64_t>(sp.gm_workers, S), sp.gm_lds, s, sp.gm_deep));
+                    // (a register bin's LPs all go to one streaming kernel)
+                    SolvePlan one = sp;
+                    (h->opt.layout == BLP_LAYOUT_COLUMN ? one.n_gm : one.n_pend) = 0;
+                    HIP_TRY(h, launch_streaming(one, Q, S, s));
                 }
                 HIP_TRY(h, hipEventRecord(e1, s));
                 HIP_TRY(h, hipEventSynchronize(e1));

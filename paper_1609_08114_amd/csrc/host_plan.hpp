@@ -37,6 +37,7 @@ struct PlanIn {
     int force = -1;              // -1 automatic, -2 streaming only, >= 0 one variant
     bool remap_streams = false;  // the autotuner sends some register bin to the streaming kernel
     bool stream_all = false;     // size the workspace as if every simplex LP could stream
+    bool (*pend)(int m, int n) = nullptr;  // LPs the pending-pivot streaming kernel takes (NULL: none)
     bool lpc = true;             // the largest-coefficient rule (type-1-only variants take LPs)
 };
 
@@ -52,6 +53,7 @@ struct Plan {
     int max_m = 0, max_n = 0, max_cols = 0;  // over the simplex LPs
     int64_t max_slot = 0;      // largest streaming tableau, doubles (16-row-aligned leading dimension)
     int64_t n_may_stream = 0;  // simplex LPs no register variant is sure to hold
+    int64_t n_may_pend = 0;    // those of them that the pending-pivot streaming kernel takes
     bool gm_deep = false;      // some LP fits no register tile even without artificial columns
     int box_n = 0;             // shared box: its length
 };
@@ -80,7 +82,7 @@ inline int plan_batch(const PlanIn& in, Plan& p) {
     p.n.assign(in.n, in.n + nmeta);
     p.kind.assign(in.kind, in.kind + nmeta);
     p.any_simplex = p.any_box = p.gm_deep = false;
-    p.n_box = p.tot_a = p.tot_m = p.tot_n = p.max_slot = p.n_may_stream = 0;
+    p.n_box = p.tot_a = p.tot_m = p.tot_n = p.max_slot = p.n_may_stream = p.n_may_pend = 0;
     p.max_m = p.max_n = p.max_cols = p.box_n = 0;
     // no register tile holds the LP even without artificial columns
     auto sure_stream = [&](int m, int n) {
@@ -115,7 +117,10 @@ inline int plan_batch(const PlanIn& in, Plan& p) {
             p.max_n = std::max(p.max_n, n);
             p.max_cols = std::max(p.max_cols, n + m + 1);
             p.max_slot = std::max<int64_t>(p.max_slot, (int64_t)((m + 2 + 15) / 16) * 16 * (n + m + 1));
-            if (!sure_register(m, n)) ++p.n_may_stream;
+            if (!sure_register(m, n)) {
+                ++p.n_may_stream;
+                if (in.pend && in.pend(m, n)) ++p.n_may_pend;
+            }
             if (sure_stream(m, n)) p.gm_deep = true;
         } else if (kd == 1) {
             if (m != 0 || n < 1)
@@ -137,6 +142,7 @@ inline int plan_batch(const PlanIn& in, Plan& p) {
     }
     if (uni) {
         p.n_may_stream *= K;
+        p.n_may_pend *= K;
         p.n_box *= K;
         p.tot_a *= K;
         p.tot_m *= K;

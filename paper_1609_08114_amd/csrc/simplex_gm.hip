@@ -101,6 +101,10 @@ __global__ void __launch_bounds__(NW * 64) simplex_gm_kernel(KParams P) {
         const LpRef L = lp_ref(P, k);
         const LpRef Lin = lp_in(P, L);  // constraint reads
         const int m = L.m, n = L.n;
+        if (P.skip_pend && pend_shape(m, n)) {
+            __syncthreads();
+            continue;
+        }
         if (m > ld - 2 || n + 1 > cg_max) {  // never routed here; no LDS write past the arrays
             write_numerical<NT>(P, L, k, t, ST_INTERNAL);
             __syncthreads();

@@ -47,45 +47,43 @@ __device__ __forceinline__ int art_count(const ArtLoads& a, int m, int i0, int l
 // variant v, loaded once per wave, so that choosing an LP's variant is one
 // compare per lane and one wave reduction instead of a loop of table loads.
 struct LaneVariant {
-    int rows, cols, type1, remap;
+    int rows, cols, type1, remap, key, sum;
     int64_t min_count;
 };
 __device__ __forceinline__ LaneVariant lane_variant(const VariantTable& vt, int lane) {
-    LaneVariant r{0, 0, 1, 0, INT64_MAX};  // lanes past the table never fit
+    LaneVariant r{0, 0, 1, 0, 0, 0, INT64_MAX};  // lanes past the table never fit
     if (lane < vt.nreg) {
         r.rows = vt.rows[lane];
         r.cols = vt.cols[lane];
         r.type1 = vt.type1[lane];
         r.remap = vt.remap[lane];
+        r.key = vt.key[lane];
+        r.sum = vt.sum[lane];
         r.min_count = vt.min_count[lane];
     }
     return r;
 }
 // The LP's bin (all 64 lanes active, result wave-uniform): the forced
-// variant if it holds the LP; else the variant of smallest area that holds
-// it (the first of equal areas; the area times 32 plus the lane is the key of
-// a wave minimum), then the autotuner's remap of that variant.
+// variant if it holds the LP; else the variant of smallest key that holds it
+// (the first of equal keys; the key times 32 plus the lane goes through a
+// wave minimum), then the autotuner's remap of that variant (unless this call
+// cannot use it: a table entry of 0 rows).
 __device__ __forceinline__ int bin_of(const VariantTable& vt, const LaneVariant& lv, int lane, const LpRef& L,
                                       int nart) {
     const int rows = L.m + 2, cols = L.n + nart + 1;
     // a variant for LPs without artificial rows under the largest-
     // coefficient rule takes only those
     const bool t1 = nart == 0 && vt.lpc;
-    if (vt.force >= 0) {
-        const int f = vt.force;
-        if (f < vt.nreg && __builtin_amdgcn_readlane(lv.rows, f) >= rows &&
-            __builtin_amdgcn_readlane(lv.cols, f) >= cols && (t1 || !__builtin_amdgcn_readlane(lv.type1, f)))
-            return f;
-        return vt.nreg;
-    }
+    const bool holds =
+        lane < vt.nreg && lv.rows >= rows && lv.cols >= cols && L.n + L.m <= lv.sum && (t1 || !lv.type1);
+    if (vt.force >= 0) return (__ballot(holds) >> vt.force) & 1ull ? vt.force : vt.nreg;
     if (vt.force != -1) return vt.nreg;  // streaming only
-    const bool fit = lane < vt.nreg && lv.rows >= rows && lv.cols >= cols && (t1 || !lv.type1) &&
-                     vt.count >= lv.min_count;
-    const int best = wave_min_i32(fit ? ((lv.rows * lv.cols) << 5) | lane : INT_MAX);
+    const int best = wave_min_i32(holds && vt.count >= lv.min_count ? (lv.key << 5) | lane : INT_MAX);
     if (best == INT_MAX) return vt.nreg;
     int bin = best & 31;
     const int r = __builtin_amdgcn_readlane(lv.remap, bin);
-    if (r >= vt.nreg || t1 || !__builtin_amdgcn_readlane(lv.type1, r)) bin = r;
+    if (r >= vt.nreg || (__builtin_amdgcn_readlane(lv.rows, r) > 0 && (t1 || !__builtin_amdgcn_readlane(lv.type1, r))))
+        bin = r;
     return bin;
 }
 

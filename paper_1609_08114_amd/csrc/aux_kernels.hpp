@@ -8,7 +8,7 @@
 
 namespace blp {
 
-constexpr int kMaxVariants = 24;  // < 32: the classify kernel keys a variant by area * 32 + index
+constexpr int kMaxVariants = 24;  // < 32: the classify kernel keys a variant by key * 32 + index
 // Widest uniform hyperbox served by the LDS-transposing kernel (LDS per wave:
 // 2 * 64 * (n + 1) doubles).
 constexpr int kBoxTileMaxN = 48;
@@ -22,6 +22,8 @@ struct VariantTable {
     int cols[kMaxVariants];
     int remap[kMaxVariants];  // autotuned replacement of each variant (nreg = streaming)
     int type1[kMaxVariants];  // 1: the variant takes only LPs without artificial rows under LPC
+    int key[kMaxVariants];    // the fitting variant of smallest key takes the LP
+    int sum[kMaxVariants];    // largest n + m
     int64_t min_count[kMaxVariants];  // automatic choice: only for batches of at least this many LPs
     int lpc;                  // 1: the largest-coefficient rule (else the random rule)
 };
@@ -127,10 +129,23 @@ template <int R, int C, int NWV, int WPE>
 const void* kernel_ptr_lane();
 
 // Streaming kernel with pending pivots (simplex_pend.hip): LPs of
-// pend_shape(), P.ws_lds doubles of dynamic LDS for the pending factors.
-hipError_t launch_pend(const KParams& P, int grid, size_t lds_bytes, hipStream_t s);
-const void* pend_kernel_ptr();
-int pend_threads();
+// pend_shape(), P.ws_lds doubles of dynamic LDS for the pending factors.  A
+// tile holds LPs of up to rows() rows and slots() = n + m columns.
+struct PendTile {
+    int waves, rows_per, slots_per;  // waves per workgroup; rows and column slots per thread
+    int tiles;                       // slot tiles a wave flushes at a time
+    int pivots;                      // pending pivots to leave LDS for
+    int wpe;                         // waves per SIMD that the registers allow
+    constexpr int rows() const { return waves * 64 * rows_per; }
+    constexpr int slots() const { return waves * 64 * slots_per; }
+};
+// One wave holds LPs of up to 64 rows without a barrier; 128 rows take two
+// waves rather than one with two rows per lane (10.4 against 13.0 ms on 4,000
+// two-phase LPs 100 x 100: the flush needs the waves), 256 four, 512 eight.
+constexpr PendTile kPendTiles[] = {{1, 1, 2, 4, 12, 3}, {2, 1, 2, 4, 8, 3}, {4, 1, 2, 4, 12, 3}, {8, 1, 2, 2, 16, 4}};
+constexpr int kPendTileCount = (int)(sizeof(kPendTiles) / sizeof(kPendTiles[0]));
+hipError_t launch_pend(const KParams& P, int tile, int grid, size_t lds_bytes, hipStream_t s);
+const void* pend_kernel_ptr(int tile);
 
 // Streaming kernel (simplex_gm.hip).
 // deep: the launch's bin is known not to be empty: for tableaux of up to 512

@@ -78,6 +78,17 @@ struct KParams {
     uint64_t seed;
 };
 
+// The launch's parameters read again from the kernel-argument segment (a
+// kernel's only argument is its KParams).  A kernel that keeps all of them in
+// scalar registers across its pivot loop spills half of them to lanes of
+// vector registers, and the loop pays for the reloads; a section that reads its own copy holds only
+// what it uses, while it uses it.
+__device__ __forceinline__ KParams kparams() {
+    auto p = __builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(p));  // a new pointer: the loads stay in this section
+    return *(const KParams*)p;
+}
+
 // LPs that the streaming kernel with pending pivots takes (simplex_pend.hip:
 // one row and two column slots per thread of 512, whatever the number of
 // artificial rows); the others stay with the one that streams the tableau at

@@ -124,7 +124,7 @@ struct blp_handle_s {
     int nreg = 0;
     void* scratch = nullptr;  // this device's copy of the static scratch (allocation-free entry point)
     std::vector<int> reg_workers;  // persistent grid per variant
-    size_t pend_static = 0;        // static LDS of the pending-pivot streaming kernel, bytes
+    size_t pend_static[kPendTileCount] = {};  // static LDS of the pending-pivot streaming kernels, bytes
     int direct_v = -1;  // the last solve's one-launch variant (no binning), or -1
     // device buffers
     DevBuf meta;     // m, n, kind (int32) + a_off, row_off, col_off (int64) for non-uniform batches
@@ -132,6 +132,7 @@ struct blp_handle_s {
     DevBuf binid, list;
     DevBuf olist;  // non-uniform batches: the work lists in largest-first order (what the kernels pop)
     DevBuf ws;       // streaming-kernel workspace
+    DevBuf pend_ws[kPendTileCount];  // workspaces of the pending-pivot classes (kPendTiles index)
     DevBuf own_status, own_iters, own_obj, own_x, own_y;
     // last solve
     bool solved = false;
@@ -222,8 +223,46 @@ static blp_error fail(blp_handle h, blp_error code, const char* fmt, ...);
 // scheduler sends to variant v?
 static bool can_replace(blp_handle h, int w, int v) {
     if (w >= h->nreg) return true;
-    return h->variants[w].max_rows >= h->variants[v].max_rows && h->variants[w].max_cols >= h->variants[v].max_cols &&
-           (!h->variants[w].type1_only || h->variants[v].type1_only);
+    const RegVariant &a = h->variants[w], &b = h->variants[v];
+    const int sum = std::min(b.max_sum, b.max_rows - 2 + b.max_cols - 1);  // v's largest n + m
+    return a.max_rows >= b.max_rows && a.max_cols >= b.max_cols && a.max_sum >= sum &&
+           (!a.type1_only || b.type1_only);
+}
+
+// Does variant v hold an LP of m rows, n columns and nart artificial rows?
+static bool holds(const RegVariant& v, int m, int n, int nart) {
+    return v.max_rows >= m + 2 && v.max_cols >= n + nart + 1 && n + m <= v.max_sum;
+}
+
+// May this call use variant v?  The pending-pivot classes need workspaces of
+// their own: not with mem_limit, nor from the static scratch.
+static bool usable(blp_handle h, int v, bool limited) { return h->variants[v].pend < 0 || !limited; }
+
+// Selection key of variant v for a batch of `count` LPs: the fitting variant
+// of smallest key takes an LP.  A register tile's key is its area.  A
+// pending-pivot class costs more latency per pivot than the 112 x 112 block
+// tile (area 12,544) and less CU time: with enough LPs to fill its workgroups
+// it comes right after the 32 x 32 tile, else right after that block tile.
+// Measured (us, block tile and class): two-phase 47 x 61, 1,024 LPs 1,134 and
+// 1,480, 2,048 LPs 1,998 and 908; one-phase 100 x 100, 2,048 LPs 240 and 253,
+// 50,000 LPs 3,680 and 3,020; one-phase 50 x 50, 8,000 LPs 531 (64 x 64 row
+// tile) and 216.  Below, at 20 x 20: the 32 x 32 row tile 443 and 501.
+static int variant_key(blp_handle h, int v, int64_t count) {
+    const RegVariant& rv = h->variants[v];
+    if (rv.pend < 0) return rv.max_rows * rv.max_cols;
+    const int64_t per_cu[] = {6, 10};  // LPs per CU from which the class comes first
+    const bool full = rv.pend < 2 && count >= per_cu[rv.pend] * h->cu_count;
+    return (full ? 32 * 32 : 112 * 112) + 1 + rv.pend;
+}
+
+// The automatic choice never takes variant v for a batch of `count` LPs: one of
+// smaller key holds everything that v holds.
+static bool superseded(blp_handle h, int v, int64_t count, bool limited) {
+    for (int w = 0; w < h->nreg; ++w)
+        if (w != v && usable(h, w, limited) && variant_key(h, w, count) < variant_key(h, v, count) &&
+            !h->variants[w].type1_only && h->variants[w].lps_per_block == 1 && can_replace(h, w, v))
+            return true;
+    return false;
 }
 
 // Smallest batch for which the automatic choice may use variant v: a variant
@@ -240,6 +279,7 @@ static int64_t auto_min_count(blp_handle h, int v) {
 static int reg_grid(blp_handle h, int v, int64_t lps) {
     const int64_t per = h->variants[v].lps_per_block;
     const int64_t need = (lps + per - 1) / per;
+    if (h->variants[v].pend >= 0) return (int)std::min<int64_t>(need, INT32_MAX);  // (bounded by launch_variant)
     return (int)std::max<int64_t>(1, std::min<int64_t>(h->reg_workers[v], need));
 }
 
@@ -353,14 +393,17 @@ blp_error blp_create(blp_handle* out, const blp_options* opt) {
         if (o.workers_per_cu > 0) occ = std::min(occ, (int)o.workers_per_cu);
         h->reg_workers.push_back(occ * h->cu_count);
     }
-    hipFuncAttributes pa{};
-    if (hipFuncGetAttributes(&pa, pend_kernel_ptr()) != hipSuccess ||
-        hipFuncSetAttribute(pend_kernel_ptr(), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(h->lds_per_block - pa.sharedSizeBytes)) != hipSuccess) {
-        delete h;
-        return BLP_ERR_HIP;
+    for (int i = 0; i < kPendTileCount; ++i) {
+        hipFuncAttributes pa{};
+        const void* fn = pend_kernel_ptr(i);
+        if (hipFuncGetAttributes(&pa, fn) != hipSuccess ||
+            hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(h->lds_per_block - pa.sharedSizeBytes)) != hipSuccess) {
+            delete h;
+            return BLP_ERR_HIP;
+        }
+        h->pend_static[i] = pa.sharedSizeBytes;
     }
-    h->pend_static = pa.sharedSizeBytes;
 #ifdef BLP_PHASE_TIMERS
     if (hipMalloc(&h->timers, TM_SLOTS * sizeof(unsigned long long)) == hipSuccess)
         (void)hipMemset(h->timers, 0, TM_SLOTS * sizeof(unsigned long long));
@@ -432,6 +475,7 @@ void blp_destroy(blp_handle h) {
     h->list.release();
     h->olist.release();
     h->ws.release();
+    for (DevBuf& b : h->pend_ws) b.release();
     h->own_status.release();
     h->own_iters.release();
     h->own_obj.release();
@@ -486,17 +530,30 @@ static void gm_lds_plan(blp_handle h, int ld, int cols, bool deep, bool shared, 
     *tab = (int32_t)t;
 }
 
-// Workgroups per CU of the pending-pivot streaming kernel and the dynamic LDS
-// of each (its pending factors; more pivots fit the larger share).  Two per CU
-// hide each other's memory latency; a batch that leaves CUs with one LP at
-// most gets the whole CU's LDS for it.
-static int pend_plan(blp_handle h, int64_t lps, size_t* bytes) {
-    int occ = lps > h->cu_count ? 2 : 1;
-    if (h->opt.workers_per_cu > 0) occ = std::min(occ, (int)h->opt.workers_per_cu);
-    // (LDS is handed out in units of at most 2 KiB)
-    const size_t share = std::min(h->lds_per_cu / (size_t)occ, h->lds_per_block) & ~(size_t)2047;
-    *bytes = share - h->pend_static;
-    return occ;
+// Launch shape of the pending-pivot kernel for LPs of at most m rows and
+// n + m columns: the given tile or the next that holds them, as many
+// workgroups per CU as leave each the LDS for the tile's number of pending
+// pivots (with half of the rows artificial).
+struct PendPlan {
+    int tile = 0, occ = 1;  // kPendTiles index, workgroups per CU
+    size_t lds = 0;         // dynamic LDS of a workgroup, bytes
+};
+static PendPlan pend_plan(blp_handle h, int64_t lps, int m, int cols, int tile = 0) {
+    PendPlan p;
+    p.tile = tile;
+    while (p.tile + 1 < kPendTileCount && (m > kPendTiles[p.tile].rows() || cols > kPendTiles[p.tile].slots())) ++p.tile;
+    const PendTile& T = kPendTiles[p.tile];
+    const size_t rows = (size_t)(m + 15) / 16 * 16 + (size_t)(cols - m / 2 + 15) / 16 * 16;
+    const size_t need = rows * (T.pivots + 2) * 8 + h->pend_static[p.tile];
+    p.occ = (int)std::max<size_t>(
+        1, std::min<size_t>(4 * T.wpe / T.waves, h->lds_per_cu / ((need + 1279) / 1280 * 1280)));
+    if (T.waves == 2 && p.occ > 1) p.occ &= ~1;  // the same number of waves on every SIMD
+    if (lps <= h->cu_count) p.occ = 1;
+    if (h->opt.workers_per_cu > 0) p.occ = std::min(p.occ, (int)h->opt.workers_per_cu);
+    // (LDS is handed out in units of 1,280 bytes)
+    const size_t share = std::min(h->lds_per_cu / (size_t)p.occ, h->lds_per_block) / 1280 * 1280;
+    p.lds = share - h->pend_static[p.tile];
+    return p;
 }
 
 // Everything one solve needs after validation.
@@ -508,10 +565,17 @@ struct SolvePlan {
     bool gm_deep = false;  // the streaming kernel's deep instantiation (deep loads, on-chip columns)
     int64_t n_pend = 0, n_gm = 0;  // LPs that may reach each streaming kernel
     int pend_workers = 0;
-    size_t pend_lds = 0;
+    PendPlan pend;
+    struct PendClass {  // a pending-pivot size class: launch shape, workgroups, workspace
+        PendPlan plan;
+        int workers = 0;
+        double* ws = nullptr;
+        int64_t slot = 0;
+    } cls[kPendTileCount];
     bool gm_shared = false;  // register kernels may run beside it (keep LDS for them)
     size_t gm_lds = 0;
     std::vector<char> maybe;  // register variants that can receive LPs
+    bool limited = false;     // no workspaces beyond the planned buffers (mem_limit, static scratch)
     int direct_v = -1;        // >= 0: one launch of this variant, LP k in workgroup k, no binning
     bool may_stream = false;  // some simplex LP may reach the streaming kernel
     // device buffers of this solve (the handle's own, or carved from an arena)
@@ -553,10 +617,12 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
     // per-class kernel times report this solve's classes only
     std::fill(h->ev_used.begin(), h->ev_used.end(), (char)0);
     std::vector<VariantShape> shapes((size_t)h->nreg);
+    const bool limited = arena || h->opt.mem_limit > 0;
     bool remap_streams = false;
     for (int v = 0; v < h->nreg; ++v) {
-        shapes[v] = {h->variants[v].max_rows, h->variants[v].max_cols, h->variants[v].type1_only,
-                     auto_min_count(h, v)};
+        const RegVariant& rv = h->variants[v];
+        shapes[v] = {usable(h, v, limited) ? rv.max_rows : 0, rv.max_cols, rv.type1_only, auto_min_count(h, v),
+                     rv.max_sum};
         remap_streams |= h->remap[v] >= h->nreg;
     }
     PlanIn in;
@@ -679,6 +745,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
     P.bin_head = bin_count + heads_at(nbins);
     if (h->opt.profile) HIP_TRY(h, h->ensure_events(nbins + 1));
 
+    sp.limited = limited;
     sp.uni = uni;
     sp.any_simplex = any_simplex;
     sp.any_box = any_box;
@@ -698,7 +765,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
     // only those chosen for some n_art in [0, m]; otherwise all.
     sp.maybe.assign(nreg, 0);
     if (h->opt.variant >= 0) {
-        sp.maybe[h->opt.variant] = 1;
+        sp.maybe[h->opt.variant] = usable(h, h->opt.variant, limited) ? 1 : 0;
     } else if (h->opt.variant == -1 && any_simplex) {
         if (uni) {
             const int m = h->plan.m[0], n = h->plan.n[0];
@@ -707,9 +774,9 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
                 int best = -1;
                 long barea = -1;
                 for (int v = 0; v < nreg; ++v)
-                    if (h->variants[v].max_rows >= m + 2 && h->variants[v].max_cols >= n + nart + 1 &&
+                    if (usable(h, v, limited) && holds(h->variants[v], m, n, nart) &&
                         (t1 || !h->variants[v].type1_only) && K >= auto_min_count(h, v)) {
-                        long a = (long)h->variants[v].max_rows * h->variants[v].max_cols;
+                        const long a = variant_key(h, v, K);
                         if (barea < 0 || a < barea) {
                             barea = a;
                             best = v;
@@ -717,12 +784,18 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
                     }
                 if (best >= 0) {
                     const int r = h->remap[best];
-                    const int to = (r >= nreg || t1 || !h->variants[r].type1_only) ? r : best;
+                    const int to =
+                        r >= nreg || (usable(h, r, limited) && (t1 || !h->variants[r].type1_only)) ? r : best;
                     if (to < nreg) sp.maybe[to] = 1;
                 }
             }
         } else {
-            std::fill(sp.maybe.begin(), sp.maybe.end(), 1);
+            for (int v = 0; v < nreg; ++v) {
+                if (!usable(h, v, limited) || superseded(h, v, K, limited)) continue;
+                sp.maybe[v] = 1;
+                const int r = h->remap[v];
+                if (r < nreg && usable(h, r, limited)) sp.maybe[r] = 1;
+            }
         }
     }
     // A uniform batch small enough that every LP gets a place of its own at
@@ -739,7 +812,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         for (int v = 0; v < nreg; ++v) {
             const RegVariant& rv = h->variants[v];
             const int64_t per = rv.lps_per_block;
-            if (rv.max_rows >= m + 2 && rv.max_cols >= n + m + 1 && !rv.type1_only && h->remap[v] == v &&
+            if (holds(rv, m, n, m) && rv.pend < 0 && !rv.type1_only && h->remap[v] == v &&
                 K <= (int64_t)h->reg_workers[v] * per && (per == 1 || K >= auto_min_count(h, v))) {
                 const long a = (long)rv.max_rows * rv.max_cols;
                 if (barea < 0 || a < barea) {
@@ -748,6 +821,19 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
                 }
             }
         }
+    }
+    // Pending-pivot classes: a workspace slot per workgroup for the largest
+    // LP that the class may get.
+    for (int v = 0; v < nreg; ++v) {
+        const int i = h->variants[v].pend;
+        if (i < 0 || limited || !any_simplex || sp.direct_v >= 0 || !(sp.maybe[v] || stream_all)) continue;
+        SolvePlan::PendClass& c = sp.cls[i];
+        const int mc = std::min(max_m, kPendTiles[i].rows()), cc = std::min(max_cols - 1, kPendTiles[i].slots());
+        c.plan = pend_plan(h, K, mc, cc, i);
+        c.workers = (int)std::min<int64_t>((int64_t)c.plan.occ * h->cu_count, K);
+        c.slot = (int64_t)((mc + 3) & ~3) * cc;
+        HIP_TRY(h, h->pend_ws[i].reserve(sizeof(double) * (size_t)c.slot * (size_t)c.workers));
+        c.ws = h->pend_ws[i].as<double>();
     }
     // Streaming-kernel geometry: worst case over the batch's simplex LPs.
     if (any_simplex) {
@@ -767,8 +853,8 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         sp.gm_workers = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * h->cu_count,
                                                                     stream_all ? n_may_stream : sp.n_gm));
         if (sp.n_pend > 0) {
-            const int64_t w = (int64_t)pend_plan(h, sp.n_pend, &sp.pend_lds) * h->cu_count;
-            sp.pend_workers = (int)std::min<int64_t>(w, sp.n_pend);
+            sp.pend = pend_plan(h, sp.n_pend, std::min(max_m, kPendRows), std::min(max_cols - 1, kPendSlots));
+            sp.pend_workers = (int)std::min<int64_t>((int64_t)sp.pend.occ * h->cu_count, sp.n_pend);
         }
         int slots = std::max(sp.gm_workers, sp.pend_workers);
         const size_t slot = (size_t)max_slot;
@@ -795,16 +881,18 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
     return BLP_SUCCESS;
 }
 
-static VariantTable variant_table(blp_handle h, int64_t count) {
+static VariantTable variant_table(blp_handle h, int64_t count, bool limited) {
     VariantTable vt{};
     vt.nreg = h->nreg;
     vt.count = count;
     vt.force = h->opt.variant;
     for (int v = 0; v < h->nreg && v < kMaxVariants; ++v) {
-        vt.rows[v] = h->variants[v].max_rows;
+        vt.rows[v] = usable(h, v, limited) ? h->variants[v].max_rows : 0;  // 0: never fits
         vt.cols[v] = h->variants[v].max_cols;
         vt.remap[v] = h->remap[v];
         vt.type1[v] = h->variants[v].type1_only;
+        vt.key[v] = variant_key(h, v, count);
+        vt.sum[v] = h->variants[v].max_sum;
         vt.min_count[v] = auto_min_count(h, v);
     }
     vt.lpc = h->opt.pivot_rule == BLP_RULE_LPC;
@@ -821,7 +909,7 @@ static blp_error enqueue_binning(blp_handle h, SolvePlan& sp, hipStream_t s) {
     // zero the counters and the striped bin counters (bin_off is rewritten)
     int32_t* stripes = bin_count + stripes_at(nbins);
     HIP_TRY(h, launch_reset(bin_count, (int)counter_ints(nbins), s));
-    HIP_TRY(h, launch_classify(sp.P, variant_table(h, sp.P.count), sp.binid, stripes, s));
+    HIP_TRY(h, launch_classify(sp.P, variant_table(h, sp.P.count, sp.limited), sp.binid, stripes, s));
     HIP_TRY(h, launch_bin_offsets(stripes, bin_count, const_cast<int32_t*>(sp.P.bin_off), nbins, s));
     HIP_TRY(h, launch_scatter(sp.P.count, nbins, sp.binid, sp.P.bin_off, bin_fill, sp.list, s));
     // a uniform batch has one cost per bin; otherwise the kernels pop the
@@ -840,15 +928,29 @@ static hipError_t launch_streaming(const SolvePlan& sp, const KParams& P, int64_
     const bool both = sp.n_pend > 0 && sp.n_gm > 0;
     if (sp.n_pend > 0) {
         KParams Q = P;
-        Q.ws_lds = (int32_t)(sp.pend_lds / sizeof(double));
-        const hipError_t e =
-            launch_pend(Q, (int)std::min<int64_t>(P.direct ? grid : sp.pend_workers, grid), sp.pend_lds, s);
+        Q.ws_lds = (int32_t)(sp.pend.lds / sizeof(double));
+        const hipError_t e = launch_pend(Q, sp.pend.tile, (int)std::min<int64_t>(P.direct ? grid : sp.pend_workers, grid),
+                                         sp.pend.lds, s);
         if (e != hipSuccess || !both) return e;
     }
     KParams Q = P;
     Q.skip_pend = both ? 1 : 0;
     if (both) Q.bin_head += kHeadStride;
     return launch_gm(Q, (int)std::min<int64_t>(P.direct ? grid : sp.gm_workers, grid), sp.gm_lds, s, sp.gm_deep);
+}
+
+// Variant v's launch over Q's work list, `grid` workgroups at most (a
+// pending-pivot class: no more than its workspace has slots).
+static hipError_t launch_variant(blp_handle h, const SolvePlan& sp, int v, const KParams& P, int64_t grid,
+                                 hipStream_t s) {
+    const int i = h->variants[v].pend;
+    if (i < 0) return h->variants[v].launch(P, (int)grid, s);
+    const SolvePlan::PendClass& c = sp.cls[i];
+    KParams Q = P;
+    Q.ws = c.ws;
+    Q.ws_slot = c.slot;
+    Q.ws_lds = (int32_t)(c.plan.lds / sizeof(double));
+    return launch_pend(Q, c.plan.tile, (int)std::min<int64_t>(grid, c.workers), c.plan.lds, s);
 }
 
 // One persistent launch per kernel class that can receive LPs.  For a mixed
@@ -859,18 +961,24 @@ static hipError_t launch_streaming(const SolvePlan& sp, const KParams& P, int64_
 // uniform batch has one dominant class, and there the fork and join would
 // only add their own latency.  A captured sequence (graph mode) keeps every
 // class on the capturing stream.
-static constexpr int64_t kForkMinLps = 2048;
+static constexpr int64_t kForkMinLps = 256;
 static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, bool capturing = false) {
     const int nreg = h->nreg;
     const int64_t K = sp.P.count;
     KParams P = sp.P;
     P.direct = 0;
     std::vector<int> cls;  // 0..nreg-1 register variants, nreg streaming
-    for (int v = 0; v < nreg; ++v)
-        if (sp.maybe[v]) cls.push_back(v);
     // the streaming launch is left out when every LP surely fits a register
     // tile (an empty launch still costs a few microseconds on the stream)
     if (sp.any_simplex && sp.may_stream) cls.push_back(nreg);
+    for (int v = 0; v < nreg; ++v)
+        if (sp.maybe[v]) cls.push_back(v);
+    // largest LPs first: a launch lasts at least as long as its largest LP,
+    // and the smaller classes fill in behind it
+    const auto area = [&](int v) {
+        return v == nreg ? INT64_MAX : (int64_t)h->variants[v].max_rows * h->variants[v].max_cols;
+    };
+    std::stable_sort(cls.begin(), cls.end(), [&](int a, int b) { return area(a) > area(b); });
     const int nc = (int)cls.size();
     const bool forked = !capturing && nc > 1 && !sp.uni && K >= kForkMinLps;
     const int nf = forked ? std::min(nc - 1, (int)blp_handle_s::kForks) : 0;
@@ -886,15 +994,15 @@ static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, 
     const char* what = "";
     for (int i = 0; i < nc && err == hipSuccess; ++i) {
         const int v = cls[i];
-        // the last class (the streaming kernel when present) stays on s
-        hipStream_t st = (forked && i < nc - 1) ? h->fork[i % nf] : s;
+        // the first class (the largest LPs) stays on s
+        hipStream_t st = (forked && i > 0) ? h->fork[(i - 1) % nf] : s;
         KParams Q = P;
         Q.bin = v;
         err = h->mark(v, true, st);
         what = "event record";
         if (err == hipSuccess) {
             what = "kernel launch";
-            err = v < nreg ? h->variants[v].launch(Q, reg_grid(h, v, K), st)
+            err = v < nreg ? launch_variant(h, sp, v, Q, reg_grid(h, v, K), st)
                            : launch_streaming(sp, Q, K, st);
         }
         if (err == hipSuccess) {
@@ -944,7 +1052,9 @@ static blp_error enqueue_baseline(blp_handle h, SolvePlan& sp, hipStream_t s) {
         Q.bin = v;
         const int stream_slots = sp.n_gm == 0 ? sp.pend_workers
                                  : sp.n_pend == 0 ? sp.gm_workers : std::min(sp.gm_workers, sp.pend_workers);
-        const int64_t chunk = v == nreg ? stream_slots : (mode == BLP_MODE_GRID ? nv : 1);
+        const int pc = v < nreg ? h->variants[v].pend : -1;
+        const int64_t chunk = v == nreg ? stream_slots
+                              : mode == BLP_MODE_GRID && pc >= 0 ? sp.cls[pc].workers : (mode == BLP_MODE_GRID ? nv : 1);
         const int64_t per = v < nreg ? h->variants[v].lps_per_block : 1;  // LPs per workgroup
         HIP_TRY(h, h->mark(v, true, s));
         for (int64_t first = 0; first < nv; first += chunk) {
@@ -961,7 +1071,7 @@ static blp_error enqueue_baseline(blp_handle h, SolvePlan& sp, hipStream_t s) {
                     }
                 }
             } else {
-                HIP_TRY(h, h->variants[v].launch(Q, grid, s));
+                HIP_TRY(h, launch_variant(h, sp, v, Q, grid, s));
             }
         }
         HIP_TRY(h, h->mark(v, false, s));
@@ -982,7 +1092,10 @@ static std::vector<uint64_t> graph_signature(blp_handle h, const SolvePlan& sp, 
                                (uint64_t)(uintptr_t)P.ws, (uint64_t)P.ws_slot, (uint64_t)P.ws_ld,
                                (uint64_t)P.ws_cols, (uint64_t)(uintptr_t)P.m, (uint64_t)(uintptr_t)sp.binid,
                                (uint64_t)sp.gm_lds, (uint64_t)sp.gm_workers, (uint64_t)sp.gm_deep, (uint64_t)sp.n_pend,
-                               (uint64_t)sp.n_gm, (uint64_t)sp.pend_workers, (uint64_t)sp.pend_lds};
+                               (uint64_t)sp.n_gm, (uint64_t)sp.pend_workers, (uint64_t)sp.pend.lds, (uint64_t)sp.pend.tile};
+    for (const SolvePlan::PendClass& c : sp.cls)
+        for (uint64_t x : {(uint64_t)(uintptr_t)c.ws, (uint64_t)c.slot, (uint64_t)c.workers, (uint64_t)c.plan.lds})
+            g.push_back(x);
     for (int v = 0; v < h->nreg; ++v) g.push_back((uint64_t)sp.maybe[v] | ((uint64_t)h->remap[v] << 8));
     g.push_back((uint64_t)(int64_t)sp.direct_v);
     g.push_back((uint64_t)P.pivot_rule);
@@ -1392,11 +1505,20 @@ static blp_error solve_shared_forced(blp_handle h, KParams& P, int rows, int col
     for (int i = 0; i < m; ++i) nart += (hs[i] ? -hb[i] : hb[i]) < 0.0;
     if (ns > 1 && 2 * close >= ns - 1 && m + 2 <= rows && n + nart + 1 <= cols) return launch_shared_warm(h, P, s);
     const int v = h->opt.variant;
-    if (h->variants[v].max_rows < m + 2 || h->variants[v].max_cols < n + nart + 1 ||
+    if (!holds(h->variants[v], m, n, nart) ||
         (h->variants[v].type1_only && (nart > 0 || h->opt.pivot_rule != BLP_RULE_LPC)))
         return fail(h, BLP_ERR_TOO_LARGE, "variant %s cannot hold the shared constraints", h->variants[v].name);
     P.shared_in = 1;
-    HIP_TRY(h, h->variants[v].launch(P, reg_grid(h, v, count), s));
+    SolvePlan sp;
+    if (const int i = h->variants[v].pend; i >= 0) {
+        SolvePlan::PendClass& c = sp.cls[i];
+        c.plan = pend_plan(h, count, m, n + m, i);
+        c.workers = (int)std::min<int64_t>((int64_t)c.plan.occ * h->cu_count, count);
+        c.slot = (int64_t)((m + 3) & ~3) * (n + m);
+        HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * (size_t)c.slot * (size_t)c.workers));
+        c.ws = h->shared_ws.as<double>();
+    }
+    HIP_TRY(h, launch_variant(h, sp, v, P, reg_grid(h, v, count), s));
     return BLP_SUCCESS;
 }
 
@@ -1471,7 +1593,8 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
     for (int v = 0; v < nreg && v < kMaxVariants; ++v) {
         rt.rows[v] = h->variants[v].max_rows;
         rt.cols[v] = h->variants[v].max_cols;
-        rt.type1[v] = h->variants[v].type1_only;
+        // (never a pending-pivot class: the streaming route picks its tile)
+        rt.type1[v] = h->variants[v].type1_only || h->variants[v].pend >= 0;
     }
     rt.tile_rows = rows;
     rt.tile_cols = cols;
@@ -1514,8 +1637,11 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
         const bool deep = true, pend = h->opt.layout == BLP_LAYOUT_COLUMN && pend_shape(m, n);
         int occ = 1;
         size_t lds = 0;
+        PendPlan pp;
         if (pend) {
-            occ = pend_plan(h, count, &lds);
+            pp = pend_plan(h, count, m, n + m);
+            occ = pp.occ;
+            lds = pp.lds;
             Q.ws_lds = (int32_t)(lds / sizeof(double));
         } else {
             gm_lds_plan(h, ld, gcols, deep, false, &lds, &Q.ws_lds, &occ);
@@ -1528,7 +1654,7 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
         Q.ws_slot = (int64_t)slot;
         Q.ws_ld = ld;
         Q.ws_cols = gcols;
-        HIP_TRY(h, pend ? launch_pend(Q, (int)workers, lds, s) : launch_gm(Q, (int)workers, lds, s, deep));
+        HIP_TRY(h, pend ? launch_pend(Q, pp.tile, (int)workers, lds, s) : launch_gm(Q, (int)workers, lds, s, deep));
     }
     HIP_TRY(h, end_call(h, s));
     return BLP_SUCCESS;
@@ -1911,13 +2037,13 @@ blp_error blp_autotune(blp_handle h, const blp_batch* B, int32_t sample, const c
         float best_ms = -1.f;
         int best = v;
         for (int w = 0; w <= nreg; ++w) {
-            if (!can_replace(h, w, v)) continue;
+            if (!can_replace(h, w, v) || (w < nreg && !usable(h, w, sp.limited))) continue;
             float ms = 0.f;
             for (int rep = 0; rep < 2; ++rep) {  // the second run is timed
                 HIP_TRY(h, launch_reset(tb + 2, 1, s));
                 HIP_TRY(h, hipEventRecord(e0, s));
                 if (w < nreg) {
-                    HIP_TRY(h, h->variants[w].launch(Q, reg_grid(h, w, S), s));
+                    HIP_TRY(h, launch_variant(h, sp, w, Q, reg_grid(h, w, S), s));
                 } else {
                     // (a register bin's LPs all go to one streaming kernel)
                     SolvePlan one = sp;

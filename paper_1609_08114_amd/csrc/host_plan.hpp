@@ -24,6 +24,9 @@ struct VariantShape {
     int rows, cols;  // largest tableau (rows incl. objective rows, columns incl. rhs)
     int type1 = 0;   // 1: takes only LPs without artificial rows under the largest-coefficient rule
     int64_t min_count = 0;  // the automatic choice takes it only for batches of at least this many LPs
+    int sum = 0x7fffffff;   // largest n + m
+    // whether it holds an LP of m rows, n columns and nart artificial rows
+    bool holds(int m, int n, int nart) const { return rows >= m + 2 && cols >= n + nart + 1 && n + m <= sum; }
 };
 
 struct PlanIn {
@@ -89,7 +92,7 @@ inline int plan_batch(const PlanIn& in, Plan& p) {
         if (in.force == -2) return true;
         for (int v = 0; v < in.nreg; ++v) {
             if (in.force >= 0 && v != in.force) continue;
-            if (in.variants[v].rows >= m + 2 && in.variants[v].cols >= n + 1 && (in.lpc || !in.variants[v].type1))
+            if (in.variants[v].holds(m, n, 0) && (in.lpc || !in.variants[v].type1))
                 return false;
         }
         return true;
@@ -99,7 +102,7 @@ inline int plan_batch(const PlanIn& in, Plan& p) {
         if (in.stream_all || in.force == -2 || in.remap_streams) return false;
         for (int v = 0; v < in.nreg; ++v) {
             if (in.force >= 0 && v != in.force) continue;
-            if (in.variants[v].rows >= m + 2 && in.variants[v].cols >= n + m + 1 && !in.variants[v].type1 &&
+            if (in.variants[v].holds(m, n, m) && !in.variants[v].type1 &&
                 (in.force >= 0 || in.count >= in.variants[v].min_count))
                 return true;
         }

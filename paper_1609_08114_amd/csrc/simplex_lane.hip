@@ -26,6 +26,7 @@ const void* kernel_ptr_lane() {
 #define BLP_REG_VARIANT(...)
 #define BLP_BLK_VARIANT(...)
 #define BLP_COLS_VARIANT(...)
+#define BLP_PEND_VARIANT(...)
 BLP_REG_VARIANT_LIST
 
 }  // namespace blp

@@ -23,6 +23,8 @@
 // ratio test -> owners of the pivot row publish it -> barrier -> divide by
 // the pivot element (Step 3's NewPivotRow) -> barrier -> register update and
 // mirrors -> barrier.
+#include <climits>
+
 #include "aux_kernels.hpp"
 #include "blp_kernels.hpp"
 #include "simplex_blk.hpp"
@@ -452,15 +454,24 @@ void shared_shape(int* rows, int* cols) {
 
 #define BLP_BLK_VARIANT(NAME, NW, GC, RB, CB, WPE)                                                    \
     {NAME, (NW) * 64, (NW) * 64 / (GC) * (RB), (GC) * (CB), &launch_blk<NW, GC, RB, CB, WPE>, \
-     &kernel_ptr_blk<NW, GC, RB, CB, WPE>, 1, 0},
+     &kernel_ptr_blk<NW, GC, RB, CB, WPE>, 1, 0, -1, INT_MAX},
 #define BLP_REG_VARIANT(NAME, NW, TC, CT, WPE)                                                                  \
     {NAME, (NW) * 64, (NW) * 64 / (TC), (TC) * (CT), &launch_reg<NW, TC, CT, WPE>, &kernel_ptr<NW, TC, CT, WPE>, \
-     1, 0},
+     1, 0, -1, INT_MAX},
 #define BLP_COLS_VARIANT(NAME, NW, GCW, RB, CB, WPE, ROWS, COLS)                                  \
     {NAME, (NW) * 64, ROWS, COLS, &launch_cols<NW, GCW, RB, CB, WPE, ROWS, COLS>,                 \
-     &kernel_ptr_cols<NW, GCW, RB, CB, WPE>, 1, 1},
+     &kernel_ptr_cols<NW, GCW, RB, CB, WPE>, 1, 1, -1, INT_MAX},
 #define BLP_LANE_VARIANT(NAME, R, C, NWV, WPE) \
-    {NAME, (NWV) * 64, R, C, &launch_lane<R, C, NWV, WPE>, &kernel_ptr_lane<R, C, NWV, WPE>, (NWV) * 64, 0},
+    {NAME, (NWV) * 64, R, C, &launch_lane<R, C, NWV, WPE>, &kernel_ptr_lane<R, C, NWV, WPE>, (NWV) * 64, 0, -1, \
+     INT_MAX},
+#define BLP_PEND_VARIANT(NAME, I)                                                                             \
+    {NAME, kPendTiles[I].waves * 64, kPendTiles[I].rows() + 2, kPendTiles[I].slots() + 1, nullptr,             \
+     &pend_tile_ptr<I>, 1, 0, I, kPendTiles[I].slots()},
+
+template <int I>
+static const void* pend_tile_ptr() {
+    return pend_kernel_ptr(I);
+}
 
 const RegVariant* reg_variants(int* count) {
     static const RegVariant table[] = {BLP_REG_VARIANT_LIST};

@@ -13,12 +13,16 @@
 //     the waves; it holds (64/GCW) RB constraint rows by waves GCW CB slots
 //     and claims the stated shape.  It takes only LPs without artificial
 //     rows under the largest-coefficient rule (type1_only).
+//   BLP_PEND_VARIANT (name, index into kPendTiles): simplex_pend_kernel, one
+//     LP per workgroup, the tableau in a workspace slot: not a register tile,
+//     but a size class of its own beside them.
 // Shapes count the objective rows and the rhs column.  The scheduler sends
-// each LP to the fitting variant of smallest area, the first in this order
-// among equal areas: the lane variants come first, a column-split variant
-// comes before the block tile of its shape (it takes the LPs it can), and
-// the row-tile w4/w8 variants (the first design, kept for comparison and the
-// autotuner) come after the block tiles of their shapes.
+// each LP to the fitting variant of smallest key, the first in this order
+// among equal keys (variant_key): the area of a register tile, so that the
+// lane variants come first, a column-split variant comes before the block tile
+// of its shape (it takes the LPs it can), and the row-tile w4/w8 variants
+// (the first design, kept for comparison and the autotuner) come after the
+// block tiles of their shapes.
 #pragma once
 
 #include "blp_kernels.hpp"
@@ -34,6 +38,8 @@ struct RegVariant {
     const void* (*kernel)();
     int lps_per_block;  // LPs a workgroup takes at once (lane kernel: one per thread)
     int type1_only;     // 1: only LPs with no artificial rows, largest-coefficient rule
+    int pend;           // kPendTiles index of a pending-pivot class (launched with a workspace), else -1
+    int max_sum;        // largest n + m (pending-pivot classes; else no limit)
 };
 
 // Host-side table of the compiled variants.
@@ -53,7 +59,10 @@ const RegVariant* reg_variants(int* count);
     BLP_BLK_VARIANT("b8_r128_c128",  8, 16, 4, 8, 2)         \
     BLP_BLK_VARIANT("b8_r160_c160",  8, 16, 5, 10, 2)        \
     BLP_REG_VARIANT("w4_r128_c112",  4, 2,  56, 2)           \
-    BLP_REG_VARIANT("w8_r128_c128",  8, 4,  32, 2)
+    BLP_REG_VARIANT("w8_r128_c128",  8, 4,  32, 2)           \
+    BLP_PEND_VARIANT("p1_r64_s128",   0)                     \
+    BLP_PEND_VARIANT("p2_r128_s256",  1)                     \
+    BLP_PEND_VARIANT("p4_r256_s512",  2)
 // clang-format on
 
 }  // namespace blp

@@ -81,3 +81,22 @@ def test_random_rule_draws_the_same_pivots():
         assert np.array_equal(a[k], b[k]), k
     for k in ("obj", "x", "y"):
         assert np.array_equal(a[k].view(np.int64), b[k].view(np.int64)), k
+
+
+@pytest.mark.parametrize("m,n,K,name", [
+    (33, 20, 1700, "p1_r64_s128"), (64, 64, 1700, "p1_r64_s128"), (64, 65, 1700, "b4_r112_c112"),
+    (65, 63, 2600, "p2_r128_s256"), (30, 100, 2600, "p2_r128_s256"), (128, 128, 2600, "p2_r128_s256"),
+    (33, 20, 1000, "w2_r64_c64"), (129, 60, 40, "p4_r256_s512"), (256, 256, 40, "p4_r256_s512"), (257, 20, 40, "streaming"),
+])
+def test_size_classes(m, n, K, name):
+    """The automatic choice at the edges of the pending-pivot classes and of
+    the batch sizes from which they come before the register tiles."""
+    import paper_1609_08114_amd as blp
+    hb = lpgen.make_batch(600 + m, np.arange(K), np.full(K, 2, np.int32), np.full(K, m, np.int32),
+                          np.full(K, n, np.int32))
+    cap = 40 if m * n > 3000 else 0
+    print(f"[pend] class of {m} x {n} x {K}", flush=True)
+    g = gpu_solve(hb, max_iter=cap)
+    names = [v[0] for v in blp.variants()] + ["streaming"]
+    assert g["bins"][names.index(name)] == K, [(a, b) for a, b in zip(names, g["bins"]) if b]
+    compare(hb, g, oracle_solve(hb, max_iter=cap), strict=True, tag=name)

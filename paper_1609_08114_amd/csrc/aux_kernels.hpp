@@ -132,17 +132,21 @@ const void* kernel_ptr_lane();
 // pend_shape(), P.ws_lds doubles of dynamic LDS for the pending factors.  A
 // tile holds LPs of up to rows() rows and slots() = n + m columns.
 struct PendTile {
-    int waves, rows_per, slots_per;  // waves per workgroup; rows and column slots per thread
-    int tiles;                       // slot tiles a wave flushes at a time
-    int pivots;                      // pending pivots to leave LDS for
-    int wpe;                         // waves per SIMD that the registers allow
-    constexpr int rows() const { return waves * 64 * rows_per; }
-    constexpr int slots() const { return waves * 64 * slots_per; }
+    int waves;   // per workgroup; a thread owns one row and two slots
+    int tiles;   // slot tiles a wave flushes at a time
+    int pivots;  // pending pivots to leave LDS for
+    int wpe;     // waves per SIMD that the registers allow
+    constexpr int rows() const { return waves * 64; }
+    constexpr int slots() const { return waves * 128; }
 };
 // One wave holds LPs of up to 64 rows without a barrier; 128 rows take two
 // waves rather than one with two rows per lane (10.4 against 13.0 ms on 4,000
 // two-phase LPs 100 x 100: the flush needs the waves), 256 four, 512 eight.
-constexpr PendTile kPendTiles[] = {{1, 1, 2, 4, 12, 3}, {2, 1, 2, 4, 8, 3}, {4, 1, 2, 4, 12, 3}, {8, 1, 2, 2, 16, 4}};
+// Three waves per SIMD up to four waves: with 128 registers for four, 4,000 of
+// 100 x 100 take 8.2 ms against 7.9, 50,000 one-phase ones 2.84 against 2.41.
+// Eight waves: one LP per CU (two take as long), and the registers for it: a
+// mixed batch of 2,000 LPs of up to 300 x 300 20.3 ms, with 128 registers 23.3.
+constexpr PendTile kPendTiles[] = {{1, 4, 12, 3}, {2, 4, 8, 3}, {4, 4, 16, 3}, {8, 4, 24, 2}};
 constexpr int kPendTileCount = (int)(sizeof(kPendTiles) / sizeof(kPendTiles[0]));
 hipError_t launch_pend(const KParams& P, int tile, int grid, size_t lds_bytes, hipStream_t s);
 const void* pend_kernel_ptr(int tile);

@@ -531,28 +531,45 @@ static void gm_lds_plan(blp_handle h, int ld, int cols, bool deep, bool shared, 
 }
 
 // Launch shape of the pending-pivot kernel for LPs of at most m rows and
-// n + m columns: the given tile or the next that holds them, as many
-// workgroups per CU as leave each the LDS for the tile's number of pending
-// pivots (with half of the rows artificial).
+// n + m columns (alone: nothing else runs meanwhile): the given tile or the
+// next that holds them, as many workgroups per CU as leave each the LDS for the
+// tile's number of pending pivots (with half of the rows artificial), and two
+// where that leaves 8.  More pending pivots mean fewer flushes, more workgroups
+// hide the latency of a pivot.
 struct PendPlan {
     int tile = 0, occ = 1;  // kPendTiles index, workgroups per CU
     size_t lds = 0;         // dynamic LDS of a workgroup, bytes
 };
-static PendPlan pend_plan(blp_handle h, int64_t lps, int m, int cols, int tile = 0) {
+// Doubles of one workspace slot for LPs of at most m rows and n + m columns
+// (whole row tiles, blocks of four slots).
+static int64_t pend_slot(int m, int cols) { return (int64_t)((m + 15) & ~15) * (((cols + 3) & ~3) | 4) + 16; }
+static PendPlan pend_plan(blp_handle h, int64_t lps, int m, int cols, bool alone, int tile = 0) {
     PendPlan p;
     p.tile = tile;
     while (p.tile + 1 < kPendTileCount && (m > kPendTiles[p.tile].rows() || cols > kPendTiles[p.tile].slots())) ++p.tile;
     const PendTile& T = kPendTiles[p.tile];
-    const size_t rows = (size_t)(m + 15) / 16 * 16 + (size_t)(cols - m / 2 + 15) / 16 * 16;
-    const size_t need = rows * (T.pivots + 2) * 8 + h->pend_static[p.tile];
-    p.occ = (int)std::max<size_t>(
-        1, std::min<size_t>(4 * T.wpe / T.waves, h->lds_per_cu / ((need + 1279) / 1280 * 1280)));
-    if (T.waves == 2 && p.occ > 1) p.occ &= ~1;  // the same number of waves on every SIMD
-    if (lps <= h->cu_count) p.occ = 1;
-    if (h->opt.workers_per_cu > 0) p.occ = std::min(p.occ, (int)h->opt.workers_per_cu);
     // (LDS is handed out in units of 1,280 bytes)
-    const size_t share = std::min(h->lds_per_cu / (size_t)p.occ, h->lds_per_block) / 1280 * 1280;
-    p.lds = share - h->pend_static[p.tile];
+    auto need = [&](int pivots) {
+        const size_t b = (size_t)(m + cols - m / 2) * pivots * sizeof(double) + h->pend_static[p.tile];
+        return (b + 1279) / 1280 * 1280;
+    };
+    auto fit = [&](int pivots) { return (int)(h->lds_per_cu / need(pivots)); };
+    p.occ = std::max(1, std::min(4 * T.wpe / T.waves, std::max(fit(T.pivots), std::min(2, fit(8)))));
+    if (T.waves == 2 && p.occ > 1) p.occ &= ~1;  // the same number of waves on every SIMD
+    size_t share;
+    if (alone) {
+        // as many at a time as the rounds over all CUs take: more would only
+        // leave each fewer pending pivots and less of the caches
+        const int64_t rounds = (lps + (int64_t)h->cu_count * p.occ - 1) / ((int64_t)h->cu_count * p.occ);
+        p.occ = (int)std::max<int64_t>(1, (lps + h->cu_count * rounds - 1) / (h->cu_count * rounds));
+        if (h->opt.workers_per_cu > 0) p.occ = std::min(p.occ, (int)h->opt.workers_per_cu);
+        share = h->lds_per_cu / (size_t)p.occ;
+    } else {
+        // other kernels run beside this one: leave them the rest of the LDS
+        share = p.occ > fit(T.pivots) ? h->lds_per_cu / (size_t)p.occ : need(T.pivots);
+        if (h->opt.workers_per_cu > 0) p.occ = std::min(p.occ, (int)h->opt.workers_per_cu);
+    }
+    p.lds = std::min(share, h->lds_per_block) / 1280 * 1280 - h->pend_static[p.tile];
     return p;
 }
 
@@ -829,9 +846,9 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         if (i < 0 || limited || !any_simplex || sp.direct_v >= 0 || !(sp.maybe[v] || stream_all)) continue;
         SolvePlan::PendClass& c = sp.cls[i];
         const int mc = std::min(max_m, kPendTiles[i].rows()), cc = std::min(max_cols - 1, kPendTiles[i].slots());
-        c.plan = pend_plan(h, K, mc, cc, i);
+        c.plan = pend_plan(h, K, mc, cc, sp.uni, i);
         c.workers = (int)std::min<int64_t>((int64_t)c.plan.occ * h->cu_count, K);
-        c.slot = (int64_t)((mc + 3) & ~3) * cc;
+        c.slot = pend_slot(mc, cc);
         HIP_TRY(h, h->pend_ws[i].reserve(sizeof(double) * (size_t)c.slot * (size_t)c.workers));
         c.ws = h->pend_ws[i].as<double>();
     }
@@ -853,11 +870,25 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         sp.gm_workers = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * h->cu_count,
                                                                     stream_all ? n_may_stream : sp.n_gm));
         if (sp.n_pend > 0) {
-            sp.pend = pend_plan(h, sp.n_pend, std::min(max_m, kPendRows), std::min(max_cols - 1, kPendSlots));
+            sp.pend = pend_plan(h, sp.n_pend, std::min(max_m, kPendRows), std::min(max_cols - 1, kPendSlots), sp.uni);
             sp.pend_workers = (int)std::min<int64_t>((int64_t)sp.pend.occ * h->cu_count, sp.n_pend);
         }
         int slots = std::max(sp.gm_workers, sp.pend_workers);
-        const size_t slot = (size_t)max_slot;
+        size_t slot = (size_t)max_slot;
+        if (sp.n_pend > 0) {
+            const size_t want =
+                std::max(slot, (size_t)pend_slot(std::min(max_m, kPendRows), std::min(max_cols - 1, kPendSlots)));
+            if (ws_budget > 0 && want * sizeof(double) > ws_budget) {  // the limit was made for `slot`
+                sp.n_gm += sp.n_pend;
+                sp.n_pend = 0;
+                gm_lds_plan(h, sp.gm_ld, sp.gm_cols, sp.gm_deep, sp.gm_shared, &sp.gm_lds, &P.ws_lds, &occ);
+                sp.gm_workers = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * h->cu_count, sp.n_gm));
+                sp.pend_workers = 0;
+                slots = sp.gm_workers;
+            } else {
+                slot = want;
+            }
+        }
         if (arena) {
             // as many workspace slots as the scratch still holds (fewer
             // persistent workgroups; the same results)
@@ -1512,9 +1543,9 @@ static blp_error solve_shared_forced(blp_handle h, KParams& P, int rows, int col
     SolvePlan sp;
     if (const int i = h->variants[v].pend; i >= 0) {
         SolvePlan::PendClass& c = sp.cls[i];
-        c.plan = pend_plan(h, count, m, n + m, i);
+        c.plan = pend_plan(h, count, m, n + m, true, i);
         c.workers = (int)std::min<int64_t>((int64_t)c.plan.occ * h->cu_count, count);
-        c.slot = (int64_t)((m + 3) & ~3) * (n + m);
+        c.slot = pend_slot(m, n + m);
         HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * (size_t)c.slot * (size_t)c.workers));
         c.ws = h->shared_ws.as<double>();
     }
@@ -1639,7 +1670,7 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
         size_t lds = 0;
         PendPlan pp;
         if (pend) {
-            pp = pend_plan(h, count, m, n + m);
+            pp = pend_plan(h, count, m, n + m, true);
             occ = pp.occ;
             lds = pp.lds;
             Q.ws_lds = (int32_t)(lds / sizeof(double));
@@ -1648,7 +1679,8 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
             if (h->opt.workers_per_cu > 0) occ = std::min(occ, (int)h->opt.workers_per_cu);
         }
         const int64_t workers = std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * h->cu_count, count));
-        const size_t slot = (size_t)ld * gcols;
+        const size_t slot =
+            pend ? std::max((size_t)ld * gcols, (size_t)pend_slot(m, n + m)) : (size_t)ld * gcols;
         HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * slot * (size_t)workers));
         Q.ws = h->shared_ws.as<double>();
         Q.ws_slot = (int64_t)slot;

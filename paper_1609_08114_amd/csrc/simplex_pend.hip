@@ -19,7 +19,7 @@
 // against fma() on normal, cancelling, denormal and signed-zero operands), so
 // it too gives the eager update's bits.
 //
-// Each thread owns RT rows (rhs, basis) and CT slots (reduced costs,
+// Each thread owns a row (rhs, basis) and two slots (reduced costs,
 // variables).  A pivot has two barriers: after every wave's best entering slot
 // is published, and after every wave's best leaving row is; LPs that one wave
 // holds have none.
@@ -32,24 +32,32 @@
 // nothing while the other factor is finite: a pivot with a non-finite entry is
 // flushed before the next one, so that all older terms are finite.
 //
-// What bounds it: for large LPs the flush's trips through the last-level cache
-// (a 200 x 200 type-2 tableau of ~480 KB, 16 pivots per flush), then the two
-// dependent memory reads and the reductions of a pivot, which several
-// workgroups per CU overlap.  Slots that an artificial variable left behind are
-// dropped at each flush (a third of a type-2 tableau in the end).  Measured
-// against the kernels that took these LPs before: 1,000 two-phase LPs 200 x
-// 200 (2,055 pivots each) 203 ms streaming at every pivot, 23.3 ms here; 4,000
-// of 100 x 100 22.0 ms in the 160 x 160 block tile, 10.4 here; 4,001 of 47 x 61
-// 3.51 ms in the 112 x 112 block tile, 1.59 here; 50,000 one-phase LPs 100 x 100
-// 3.67 ms in the block tile, 2.96 here (most of them end before the first
+// What bounds it: a pivot's chain of dependent steps (two memory reads, two
+// reductions over the LP, the pending FMAs), which several workgroups per CU
+// overlap, and the flush's trips through the last-level cache; for one-phase
+// LPs the column reads from the row-major A.  So what counts is workgroups in
+// flight, against the pending pivots that the LDS then leaves each.  Slots that
+// an artificial variable left behind are dropped at each flush (a third of a
+// type-2 tableau in the end), and the LDS that frees takes more pivots.
+// Everything that steers a pivot is in scalar registers: with a value that the
+// compiler takes for a per-lane one among them, its branches cost a sixth of
+// the time.
+// Measured against the kernels that took these LPs before: 1,000 two-phase LPs
+// 200 x 200 (2,055 pivots each) 204 ms streaming at every pivot, 20.9 ms here;
+// 4,000 of 100 x 100 22.0 ms in the 160 x 160 block tile, 7.8 here; 4,001 of 47 x
+// 61 3.53 ms in the 112 x 112 block tile, 1.45 here; 50,000 one-phase LPs 100 x
+// 100 3.67 ms in the block tile, 2.37 here (most of them end before the first
 // flush, and their tableau is never written).
 //
-// Layout of a slot: strips of four rows, in a strip blocks of 4 x 4 entries
-// (the last one 4 x (slots mod 4)), in a block row-major: element (i, j) at
-// (i / 4) 4 ns + (j / 4) 16 + (i mod 4) w + j mod 4, w the block's width.  One
-// 128-byte line then serves four rows of a column read and four slots of a
-// row read, and the 16 x 4 part of a matrix-core tile that one register holds
-// is 512 consecutive bytes.
+// Layout of a workspace slot: strips of four rows, in a strip blocks of 4 x 4
+// entries, in a block row-major: an entry's offset is its row's part plus its
+// slot's part.  One 128-byte line then serves four rows of a column read and
+// four slots of a row read, and the 16 x 4 part of a matrix-core tile that one
+// register holds is 512 consecutive bytes.  A strip is an odd number of lines
+// (and so is a slot, one line longer than its strips), or columns and
+// workgroups would meet in the same cache channels: 8,000 one-phase LPs 150 x
+// 150 take 2.1 ms without that, 1.25 with it.
+#include <type_traits>
 #include <utility>
 
 #include "aux_kernels.hpp"
@@ -61,16 +69,47 @@ namespace blp {
 
 typedef double acc4 __attribute__((ext_vector_type(4)));
 
-// a wave's candidate: key (as wave_argmax_i64), packed (id, pos), and what
-// goes with the winner
+// a byte offset past any tableau: a buffer load there reads 0, a store is dropped
+constexpr unsigned kPendOob = 0x80000000u;
+
+// A wave's candidate: key (as wave_argmax_i64), packed (id, pos), flags (bit 0:
+// the slot or row was replaced since the flush; bit 1: the wave saw a
+// non-finite pivot entry), and what goes with the winner.
 struct alignas(16) PendRec {
     int hi;
     unsigned lo;
-    int pk;
-    int aux;
-    double v0, v1, v2;
-    int nonfinite, pad;
+    int pk, flags;
+    double v0, v1, v2, pad;
 };
+
+// v's value in lane `src` (wave-uniform)
+__device__ __forceinline__ double lane_f64(double v, int src) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src),
+                            __builtin_amdgcn_readlane(__double2loint(v), src));
+}
+
+// x + a0 b0, and so on over the four terms, one rounding each
+__device__ __forceinline__ double fma4(double2 a0, double2 a1, double2 b0, double2 b1, double x) {
+    x = __builtin_fma(a0.x, b0.x, x);
+    x = __builtin_fma(a0.y, b0.y, x);
+    x = __builtin_fma(a1.x, b1.x, x);
+    return __builtin_fma(a1.y, b1.y, x);
+}
+
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <class T>
+__device__ __forceinline__ T* uniform(T* p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<T*>((uint64_t)(unsigned)uniform((int)v) |
+                                (uint64_t)(unsigned)uniform((int)(v >> 32)) << 32);
+}
+
+// x / b, kept in its branch: the compiler would rather always make both quotients
+__device__ __forceinline__ double plain_div(double x, double b) {
+    __asm__ volatile("" : "+v"(x));
+    return x / b;
+}
 
 // v, opaque to the compiler: what is computed from it is computed here, not
 // ahead of the pivot loop and then spilled across it
@@ -79,61 +118,67 @@ __device__ __forceinline__ int here(int v) {
     return v;
 }
 
-// The best of the NW waves' records, under the order of wave_argmax_i64, and
-// whether any record's non-finite flag is set; every wave computes it.
-// Returns the packed (id, pos); idx is the record.
+// The best of the NW waves' records, under the order of wave_argmax_i64; every
+// wave computes it.  (hi, lo, pk): this wave's own.  Returns the packed (id,
+// pos); flags are the winner's bit 0 and bit 1 of any wave.  The winner's wave
+// follows from its position.
 template <int NW>
-__device__ __forceinline__ int pend_best(const PendRec* rec, int lane, int& hi, unsigned& lo, int& idx,
-                                         bool& nonfinite) {
-    static_assert(NW <= 8, "one row of eight lanes");
-    const PendRec& r = rec[lane & (NW - 1)];
-    const bool in = lane < NW;
-    const int h = in ? r.hi : (int)0x80000000;
-    const unsigned l = r.lo;
-    const int pk = r.pk;
-    nonfinite = __ballot(in && r.nonfinite) != 0;
-    int v = h;
-    v = max(v, dpp_src<0xB1, 0xF>(v));
-    if (NW > 2) v = max(v, dpp_src<0x4E, 0xF>(v));
-    if (NW > 4) v = max(v, dpp_src<0x141, 0xF>(v));
-    hi = __builtin_amdgcn_readlane(v, 0);
-    uint64_t mk = __ballot(in && h == hi);
-    if (__popcll(mk) > 1) {  // equal high words: the low word, then the smallest id
-        unsigned best = 0;
-        for (uint64_t q = mk; q; q &= q - 1)
-            best = max(best, (unsigned)__builtin_amdgcn_readlane((int)l, __ffsll((long long)q) - 1));
-        mk = __ballot(in && h == hi && l == best);
-        int win = 0, wpk = PACK_NONE;
-        bool any = false;
-        for (uint64_t q = mk; q; q &= q - 1) {
-            const int c = __ffsll((long long)q) - 1, p = __builtin_amdgcn_readlane(pk, c);
-            if (!any || p < wpk) {
-                any = true;
-                wpk = p;
-                win = c;
+__device__ __forceinline__ int pend_best(const PendRec* rec, int lane, int wave, int hi, unsigned lo, int pk,
+                                         unsigned& flags) {
+    if constexpr (NW == 2) {  // against the other wave's, in scalar registers
+        const PendRec& r = rec[wave ^ 1];
+        const int ohi = __builtin_amdgcn_readfirstlane(r.hi), opk = __builtin_amdgcn_readfirstlane(r.pk);
+        const unsigned olo = (unsigned)__builtin_amdgcn_readfirstlane((int)r.lo);
+        const unsigned of = (unsigned)__builtin_amdgcn_readfirstlane(r.flags);
+        const bool other = ohi > hi || (ohi == hi && (olo > lo || (olo == lo && opk < pk)));
+        flags = (other ? of : flags) | ((flags | of) & 2u);
+        return other ? opk : pk;
+    } else {
+        static_assert(NW == 4 || NW == 8, "one row of eight lanes");
+        const PendRec& r = rec[lane & (NW - 1)];
+        const bool in = lane < NW;
+        const int h = in ? r.hi : (int)0x80000000;
+        const unsigned l = r.lo;
+        const int k = r.pk, f = r.flags;
+        int v = h;
+        v = max(v, dpp_src<0xB1, 0xF>(v));
+        v = max(v, dpp_src<0x4E, 0xF>(v));
+        if (NW > 4) v = max(v, dpp_src<0x141, 0xF>(v));
+        const int top = __builtin_amdgcn_readlane(v, 0);
+        const uint64_t nonfin = __ballot(in && (f & 2));
+        uint64_t mk = __ballot(in && h == top);
+        int idx = __ffsll((long long)mk) - 1;
+        if (__popcll(mk) > 1) {  // equal high words: the low word, then the smallest id
+            unsigned best = 0;
+            for (uint64_t q = mk; q; q &= q - 1)
+                best = max(best, (unsigned)__builtin_amdgcn_readlane((int)l, __ffsll((long long)q) - 1));
+            mk = __ballot(in && h == top && l == best);
+            idx = __ffsll((long long)mk) - 1;
+            int wpk = __builtin_amdgcn_readlane(k, idx);
+            for (uint64_t q = mk & (mk - 1); q; q &= q - 1) {
+                const int c = __ffsll((long long)q) - 1, p = __builtin_amdgcn_readlane(k, c);
+                idx = p < wpk ? c : idx;
+                wpk = p < wpk ? p : wpk;
             }
         }
-        idx = win;
-        lo = best;
-        return wpk;
+        idx = __builtin_amdgcn_readfirstlane(idx);
+        flags = ((unsigned)__builtin_amdgcn_readlane(f, idx) & 1u) | (nonfin ? 2u : 0u);
+        return __builtin_amdgcn_readlane(k, idx);
     }
-    idx = __builtin_amdgcn_readfirstlane(__ffsll((long long)mk) - 1);
-    lo = (unsigned)__builtin_amdgcn_readlane((int)l, idx);
-    return __builtin_amdgcn_readlane(pk, idx);
 }
 
-// NW waves; thread t owns the rows t + q NT (q < RT) and the slots t + c NT
-// (c < CT), NT = 64 NW; a wave flushes TC slot tiles at a time.
-template <int NW, int RT, int CT, int TC, int WPE>
+// NW waves; thread t owns row t and the slots t and t + NT, NT = 64 NW; a wave
+// flushes TC slot tiles at a time.
+template <int NW, int TC, int WPE>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 simplex_pend_kernel(KParams) {
-    constexpr int NT = NW * 64;
-    extern __shared__ __align__(16) double s_mem[];  // F (ldf x KS), then Q (ldq x KS)
+    constexpr int NT = NW * 64, CT = 2;
+    extern __shared__ __align__(16) double s_mem[];  // pending factors: F of the rows, then Q of the slots
     __shared__ PendRec rec1[NW], rec2[NW];
-    __shared__ unsigned short s_art[RT * NT];  // artificial rows in row order
-    __shared__ unsigned long long s_mask[RT * NW], s_neg[RT * NW];  // artificial rows, negated rows (bit per row)
+    __shared__ unsigned short s_art[NT];  // artificial rows in row order
+    __shared__ unsigned long long s_mask[NW], s_neg[NW];  // artificial rows, negated rows (bit per row)
     __shared__ unsigned long long s_dead[CT * NW];
-    __shared__ unsigned short s_rowmask[RT * NT / 16], s_slotmask[CT * NT / 16];
+    __shared__ unsigned short s_rowmask[NT / 16], s_slotmask[CT * NT / 16];
     __shared__ int s_ctl[2][2];
 
     const int t = threadIdx.x, lane = t & 63;
@@ -161,76 +206,84 @@ simplex_pend_kernel(KParams) {
         BLP_T(t_load0);
         const LpRef L = lp_ref(P, k);
         const LpRef Lin = lp_in(P, L);  // constraint reads
-        const int m = L.m, n = L.n;
-        if (m > RT * NT || n + m > CT * NT) continue;  // another streaming kernel's (uniform over the workgroup)
+        const int m = uniform(L.m), n = uniform(L.n);
+        if (m > NT || n + m > CT * NT) continue;  // another streaming kernel's (uniform over the workgroup)
 
         // ------------------------------------------------------------ load
-        double* const T = P.ws + (int64_t)blockIdx.x * P.ws_slot;
-        const double* const A = P.A + Lin.a_off;
+        double* const T = uniform(P.ws + (int64_t)blockIdx.x * P.ws_slot);
+        const double* const A = uniform(P.A + Lin.a_off);
         const double eps_price = P.eps_price, eps_piv = P.eps_piv;
-        const int rule = P.pivot_rule;
+        const int rule = P.pivot_rule, lds = P.ws_lds;
+        const bool rowt = t < m;
         int bad = 0;
-        double bR[RT];
-        int bs[RT];
-        unsigned neg = 0;  // bit q: this thread's row q is negated
-        bool art[RT];
-#pragma unroll
-        for (int q = 0; q < RT; ++q) {
-            const int i = t + q * NT;
-            bR[q] = 0.0;
-            bs[q] = ID_NONE;
-            art[q] = false;
-            if (i < m) {
-                const double bi = P.b[Lin.row_off + i];
-                const bool ge = P.sense[Lin.row_off + i] != 0;
-                const double ble = ge ? -bi : bi;
-                art[q] = ble < 0.0;
-                neg |= (ge != art[q] ? 1u : 0u) << q;
-                bR[q] = art[q] ? -ble : ble;
-                bs[q] = art[q] ? n + m + i : n + i;
-                bad |= !isfinite(bi);
-            }
-            const unsigned long long mart = __ballot(art[q]), mneg = __ballot((neg >> q) & 1u);
-            if (lane == 0) {
-                s_mask[q * NW + wave] = mart;
-                s_neg[q * NW + wave] = mneg;
-            }
+        double bR = 0.0;
+        int bs = ID_NONE;
+        bool art = false;
+        unsigned neg = 0;  // sign bit of the row's factor
+        if (rowt) {
+            const double bi = P.b[Lin.row_off + t];
+            const bool ge = P.sense[Lin.row_off + t] != 0;
+            const double ble = ge ? -bi : bi;
+            art = ble < 0.0;
+            neg = ge != art ? 0x80000000u : 0u;
+            bR = art ? -ble : ble;
+            bs = art ? n + m + t : n + t;
+            bad = !isfinite(bi);
+        }
+        const unsigned long long mart = __ballot(art), mneg = __ballot(neg != 0);
+        if (lane == 0) {
+            s_mask[wave] = mart;
+            s_neg[wave] = mneg;
         }
         __syncthreads();
-        // artificial rows in row order: the masks before this thread's, then its own
+        // artificial rows in row order: the masks before this wave's, then its own
         int nart = 0;
 #pragma unroll
-        for (int w = 0; w < RT * NW; ++w) {
-            const unsigned long long mw = s_mask[w];
-            if (art[w / NW] && (w & (NW - 1)) == wave)
-                s_art[nart + __popcll(mw & ((1ull << lane) - 1ull))] = (unsigned short)(t + w / NW * NT);
-            nart += __popcll(mw);
+        for (int w = 0; w < NW; ++w) {
+            if (w == wave && art) s_art[nart + __popcll(mart & ((1ull << lane) - 1ull))] = (unsigned short)t;
+            nart += __popcll(s_mask[w]);
         }
         nart = __builtin_amdgcn_readfirstlane(nart);
         __syncthreads();
         const int ns0 = n + nart;  // column slots; the rhs is not one of them
         int ns = ns0;              // slots still in use (the flush drops those of artificial variables)
-        // this LP's pending factors: KP pivots of ldf + ldq entries
-        const int ldf = (m + 15) & ~15, ldq = (ns0 + 15) & ~15;
-        // (a row's or slot's factors lie together, KS = KP + 2 apart: KS / 2
-        // is odd, so 16-byte reads of consecutive rows spread over the banks)
-        const int KP = min(32, (P.ws_lds / (ldf + ldq) - 2) & ~3);
-        const int KS = KP + 2;
-        double* const F = s_mem;
-        double* const Q = s_mem + KS * ldf;
-        if (KP < 4 || (int64_t)((m + 3) & ~3) * ns0 > P.ws_slot) {  // never launched so
+        const int nsp = ((ns0 + 3) & ~3) | 4;  // slots of the workspace tableau: an odd number of blocks
+        // Pending factors: KP pivots of m + ns entries, in groups of four
+        // pivots: a group holds its four factors of row (slot) i in 32 bytes.
+        // Their two halves change places with every fourth i, so that 16-byte
+        // reads of consecutive rows spread over the LDS banks.
+        int KP, qbase;  // qbase: byte offset of Q
+        auto layout = [&]() {
+            KP = min(32, (lds / (m + ns)) & ~3);
+            qbase = KP * m * 8;
+        };
+        layout();
+        // byte offset of row (slot) i's first pair within a group of F (Q); the
+        // other pair is at this ^ 16
+        auto f_off = [](int i) __attribute__((always_inline)) { return i * 32 + ((i >> 2) & 1) * 16; };
+        auto pair = [](int off) __attribute__((always_inline)) -> double2 {
+            return *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(s_mem) + off);
+        };
+        // factor u of row i of an array with `len` rows at byte offset `base`
+        auto cell = [](int base, int len, int i, int u) __attribute__((always_inline)) -> double& {
+            return *reinterpret_cast<double*>(reinterpret_cast<char*>(s_mem) + base + ((u >> 2) * len + i) * 32 +
+                                              ((((u >> 1) ^ (i >> 2)) & 1) * 16 + (u & 1) * 8));
+        };
+        if (KP < 4 || (int64_t)((m + 15) & ~15) * nsp > P.ws_slot) {  // never launched so
             write_numerical<NT>(P, L, k, t, ST_INTERNAL);
             continue;
         }
-        const int ns4 = ns0 >> 2, nrem = ns0 & 3;
-        auto at = [&](int i, int j) __attribute__((always_inline)) -> int {
-            return (i >> 2) * (4 * ns0) + (j >> 2) * 16 + (i & 3) * ((j >> 2) == ns4 ? nrem : 4) + (j & 3);
-        };
-        const unsigned tbytes = (unsigned)((m + 3) & ~3) * (unsigned)ns0 * 8u;
+        // byte offset of (i, j) in the tableau: the row's part plus the slot's
+        auto row_part = [&](int i) __attribute__((always_inline)) { return ((i >> 2) * nsp + (i & 3)) * 32; };
+        auto slot_part = [](int j) __attribute__((always_inline)) { return (j >> 2) * 128 + (j & 3) * 8; };
+        const unsigned tbytes = (unsigned)((m + 3) & ~3) * (unsigned)nsp * 8u;
         const __amdgpu_buffer_rsrc_t wsr = __builtin_amdgcn_make_buffer_rsrc(T, (short)0, (int)tbytes, 0x00020000);
         // this LP's constraints; until the first flush they are the tableau
         const __amdgpu_buffer_rsrc_t asr = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<double*>(A), (short)0, m * n * (int)sizeof(double), 0x00020000);
+        auto buf = [](__amdgpu_buffer_rsrc_t r, unsigned vo, int so) __attribute__((always_inline)) {
+            return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)vo, so, 0));
+        };
         {
             // every entry is checked once: 16-byte loads (dword-aligned is
             // enough for them), U of them in flight per lane
@@ -244,7 +297,7 @@ simplex_pend_kernel(KParams) {
                     typedef unsigned int quad __attribute__((ext_vector_type(4)));
                     typedef double two __attribute__((ext_vector_type(2)));
                     const two w = __builtin_bit_cast(
-                        two, (quad)__builtin_amdgcn_raw_buffer_load_b128(asr, x < pairs ? x * 16 : (int)0x80000000, 0, 0));
+                        two, (quad)__builtin_amdgcn_raw_buffer_load_b128(asr, x < pairs ? x * 16 : (int)kPendOob, 0, 0));
                     v[u][0] = w[0];
                     v[u][1] = w[1];
                 }
@@ -253,25 +306,36 @@ simplex_pend_kernel(KParams) {
             }
             if ((m * n) & 1) bad |= !isfinite(A[m * n - 1]);
         }
+        // every factor +0 in F and -0 in Q: the products, -0, leave every value as it is
+        auto clear_factors = [&](int pivots) __attribute__((always_inline)) {
+            typedef double two __attribute__((ext_vector_type(2)));
+            auto fill = [&](int off, int len, double v) __attribute__((always_inline)) {
+                for (int u = 0; u < pivots; u += 4, off += len * 32) {
+                    two* const w = reinterpret_cast<two*>(reinterpret_cast<char*>(s_mem) + off);
+                    w[0] = w[1] = two{v, v};
+                }
+            };
+            if (rowt) fill(t * 32, m, 0.0);
 #pragma unroll
-        for (int q = 0; q < RT; ++q)
-            if (t + q * NT < ldf)
-                for (int u = 0; u < KP; ++u) F[(t + q * NT) * KS + u] = 0.0;
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-            if (t + c * NT < ldq)
-                for (int u = 0; u < KP; ++u) Q[(t + c * NT) * KS + u] = -0.0;
-        double dO[CT], dW[CT];
+            for (int c = 0; c < CT; ++c)
+                if (t + c * NT < ns) fill(qbase + (t + c * NT) * 32, ns, -0.0);
+        };
+        clear_factors(KP);
+        // dP: the objective row that prices (the phase-1 row first, then the
+        // objective); dS: the objective during phase 1.  A slot that cannot
+        // enter (an artificial variable's, or none) holds -inf.
+        double dP[CT], dS[CT];
         int cv[CT];
         double w0 = 0.0;
+        const double ninf = -__builtin_inf();
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const int j = t + c * NT;
-            dO[c] = dW[c] = 0.0;
+            dP[c] = dS[c] = ninf;
             cv[c] = j < n ? j : (j < ns ? n + (int)s_art[j - n] : ID_NONE);
             if (j < n) {
-                dO[c] = P.c[L.col_off + j];
-                bad |= !isfinite(dO[c]);
+                const double cj = P.c[L.col_off + j];
+                bad |= !isfinite(cj);
                 // phase-1 row: the artificial rows (signs applied) summed in row order
                 double acc = 0.0;
                 for (int q0 = 0; q0 < nart; q0 += 8) {
@@ -285,9 +349,11 @@ simplex_pend_kernel(KParams) {
                             acc = acc + ((s_neg[i >> 6] >> (i & 63)) & 1ull ? -v[u] : v[u]);
                         }
                 }
-                dW[c] = acc;
+                dP[c] = nart > 0 ? acc : cj;
+                dS[c] = cj;
             } else if (j < ns) {
-                dW[c] = -1.0;
+                dP[c] = -1.0;
+                dS[c] = 0.0;
             }
         }
         for (int q = 0; q < nart; ++q) {
@@ -296,119 +362,90 @@ simplex_pend_kernel(KParams) {
         }
         if (bad) atomicOr(&s_ctl[par][1], 1);
         __syncthreads();
-        if (s_ctl[par][1]) {
+        if (uniform(s_ctl[par][1])) {
             write_numerical<NT>(P, L, k, t, ST_NUMERICAL);
             continue;
         }
-        double zO = 0.0, zW = w0;
-        unsigned dead = 0;  // bit q: this thread's row q is redundant
+        double zP = nart > 0 ? w0 : 0.0, zS = 0.0;  // rhs cells of the objective rows
+        bool live = rowt;                           // not a redundant row
         int mode = nart > 0 ? 1 : 2;
         const int max_iter = P.max_iter > 0 ? P.max_iter : 50 * (m + n);
         const int bland_after = P.bland_after > 0 ? P.bland_after : (m > n ? m : n);
         const int id_lim = n + m;
         int iters = 0, degen = 0, st = -1, drive_r = 0;
-        int s = 0;               // pending pivots
-        unsigned rb = 0, sb = 0;  // bit q: this thread's row / slot q was replaced since the last flush
-        bool nf = false;         // this thread saw a non-finite pivot entry
+        int s = 0;                   // pending pivots
+        bool rb = false;             // this thread's row was replaced since the last flush
+        unsigned sb = 0;             // bit c: its slot c likewise
+        unsigned long long nfm = 0;  // lanes of this wave that saw a non-finite pivot entry
         bool nf_any = false;
         bool from_a = true;  // no flush yet: the tableau is A with the row signs, and the surplus columns
         int zl = -1;         // row whose older factors are still to be zeroed
+        // byte offsets of this thread's row and slots in the tableau (or in A):
+        // out of range where the entries count as 0
+        unsigned ro = rowt ? (unsigned)t * (unsigned)n * 8u : kPendOob;
+        unsigned so[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) so[c] = t + c * NT < n ? (unsigned)(t + c * NT) * 8u : kPendOob;
+        // byte offsets of its factors (clamped into the arrays)
+        const int fad = f_off(min(t, m - 1));
+        int qad[CT];
+        auto slot_factors = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < CT; ++c) qad[c] = qbase + f_off(min(t + c * NT, ns - 1));
+        };
+        slot_factors();
 
-        // row r's sign (uniform r): set when the row is negated
-        auto row_neg = [&](int r) __attribute__((always_inline)) {
-            return (bool)((s_neg[r >> 6] >> (r & 63)) & 1ull);
-        };
-        // The pending terms.  The entries past s are +0 in F and -0 in Q: their
-        // products, -0, leave every value as it is.
-        // Current column of slot e (col_new: replaced since the flush).
-        auto column = [&](int e, bool col_new, double (&f)[RT]) __attribute__((always_inline)) {
-            const int th = here(t);
-#pragma unroll
-            for (int q = 0; q < RT; ++q) {
-                const int i = th + q * NT;
-                f[q] = 0.0;
-                if (i < m && !((rb >> q) & 1u) && !col_new) {
-                    if (!from_a)
-                        f[q] = T[at(i, e)];
-                    else if (e >= n)
-                        f[q] = s_art[e - n] == i ? -1.0 : 0.0;
-                    else
-                        f[q] = (neg >> q) & 1u ? -A[i * n + e] : A[i * n + e];
-                }
-            }
-            // the last pivot row's older factors: nobody else reads them now
-            if (zl >= 0 && wave == ((zl >> 6) & (NW - 1)) && lane < s - 1) F[zl * KS + lane] = 0.0;
-            zl = -1;
-            const double* const fb = Q + e * KS;
-            const double* const fa = F + th * KS;
-            for (int kb = 0; kb < s; kb += 4) {
-                double b[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) b[u] = fb[kb + u];
-#pragma unroll
-                for (int q = 0; q < RT; ++q)
-                    if (q == 0 || m > q * NT) {
-                        const double* const a = fa + (th + q * NT < ldf ? q * NT * KS : 0) + kb;
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) f[q] = __builtin_fma(a[u], b[u], f[q]);
-                    }
-            }
-#pragma unroll
-            for (int q = 0; q < RT; ++q) f[q] = th + q * NT < m ? f[q] : 0.0;
-        };
-        // Current values of row r at this thread's slots.
+        // Current values of row r at this thread's slots (row_new: its entries count as 0).
         auto row_value = [&](int r, bool row_new, double (&x)[CT]) __attribute__((always_inline)) {
-            const bool flip = from_a && row_neg(r);
-            const int th = here(t);
 #pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                const int j = th + c * NT;
-                x[c] = 0.0;
-                if (j < ns && !row_new && !((sb >> c) & 1u)) {
-                    if (!from_a)
-                        x[c] = T[at(r, j)];
-                    else if (j >= n)
-                        x[c] = s_art[j - n] == r ? -1.0 : 0.0;
-                    else
-                        x[c] = flip ? -A[r * n + j] : A[r * n + j];
+            for (int c = 0; c < CT; ++c) x[c] = 0.0;
+            if (!row_new) {
+                if (!from_a) {
+                    const int lp = row_part(r);
+                    x[0] = buf(wsr, so[0], lp);
+                    if (ns > NT) x[1] = buf(wsr, so[1], lp);
+                } else {
+                    const bool flip = (s_neg[r >> 6] >> (r & 63)) & 1ull;
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) {
+                        const double v = buf(asr, so[c], r * n * 8);
+                        x[c] = flip && so[c] != kPendOob ? -v : v;
+                        const int j = t + c * NT;
+                        if (j >= n && j < ns && !((sb >> c) & 1u)) x[c] = s_art[j - n] == r ? -1.0 : 0.0;
+                    }
                 }
             }
-            const double* const fa = F + r * KS;
-            const double* const fq = Q + th * KS;
-            for (int kb = 0; kb < s; kb += 4) {
-                double a[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) a[u] = fa[kb + u];
-#pragma unroll
-                for (int c = 0; c < CT; ++c)
-                    if (c == 0 || ns > c * NT) {
-                        const double* const b = fq + (th + c * NT < ldq ? c * NT * KS : 0) + kb;
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) x[c] = __builtin_fma(a[u], b[u], x[c]);
-                    }
+            int fa = f_off(r), q0 = qad[0], q1 = qad[1];
+            if (ns > NT) {
+                for (int kb = 0; kb < s; kb += 4, fa += m * 32, q0 += ns * 32, q1 += ns * 32) {
+                    const double2 a0 = pair(fa), a1 = pair(fa ^ 16), b0 = pair(q0), b1 = pair(q0 ^ 16), c0 = pair(q1),
+                                  c1 = pair(q1 ^ 16);
+                    x[0] = fma4(a0, a1, b0, b1, x[0]);
+                    x[1] = fma4(a0, a1, c0, c1, x[1]);
+                }
+            } else {
+                for (int kb = 0; kb < s; kb += 4, fa += m * 32, q0 += ns * 32)
+                    x[0] = fma4(pair(fa), pair(fa ^ 16), pair(q0), pair(q0 ^ 16), x[0]);
             }
         };
         // Bring the tableau up to date.
         auto flush = [&]() __attribute__((always_inline)) {
             lds_barrier();  // the last pivot's factors have been read
             const int lh = here(lane), lr = lh >> 4, lc = lh & 15;  // row of a strip, column of a slot tile
-            if (zl >= 0 && wave == ((zl >> 6) & (NW - 1)) && lane < s - 1) F[zl * KS + lane] = 0.0;
+            if (zl >= 0 && wave == zl >> 6 && lane < s - 1) cell(0, m, zl, lane) = 0.0;
             zl = -1;
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
                 const unsigned long long ms = __ballot((sb >> c) & 1u);
                 if (lc == 0) s_slotmask[(c * NT + wave * 64 + lh) >> 4] = (unsigned short)(ms >> lh);
             }
-#pragma unroll
-            for (int q = 0; q < RT; ++q) {
-                const unsigned long long mr = __ballot((rb >> q) & 1u);
-                if (lc == 0) s_rowmask[(q * NT + wave * 64 + lh) >> 4] = (unsigned short)(mr >> lh);
-            }
+            const unsigned long long mr = __ballot(rb);
+            if (lc == 0) s_rowmask[(wave * 64 + lh) >> 4] = (unsigned short)(mr >> lh);
             __syncthreads();
             // A unit is a row tile by TC slot tiles; a wave takes every NW-th.
             // (Loading the next unit's entries meanwhile changed nothing: the
             // workgroups of a CU already overlap each other's loads.)
-            const int nr = ldf >> 4, ncg = (ns + 16 * TC - 1) / (16 * TC);
+            const int nr = (m + 15) >> 4, ncg = (ns + 16 * TC - 1) / (16 * TC);
             int R = wave, cg = 0;
             while (R >= nr) {
                 R -= nr;
@@ -416,20 +453,20 @@ simplex_pend_kernel(KParams) {
             }
             while (cg < ncg) {
                 acc4 d[TC];
-                int o[TC];  // byte offset of register 0; the next strips follow 32 ns0 bytes apart
+                unsigned o[TC];  // byte offset of register 0; the next strips follow 32 nsp bytes apart
+                int sr[4];       // (cut at the end, which the range check subtracts it from)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sr[r] = min(r * (32 * nsp), (int)tbytes);
 #pragma unroll
                 for (int c = 0; c < TC; ++c) {
                     const int j = (cg * TC + c) * 16 + lc;
-                    const int w = (j >> 2) == ns4 ? nrem : 4;
-                    o[c] = j < ns ? (16 * R * ns0 + (j >> 2) * 16 + lr * w + (j & 3)) * 8 : (int)0x80000000;
+                    o[c] = j < ns ? (unsigned)(row_part(16 * R + lr) + slot_part(j)) : kPendOob;
                 }
                 if (!from_a) {
 #pragma unroll
                     for (int c = 0; c < TC; ++c)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            d[c][r] = __builtin_bit_cast(
-                                double, __builtin_amdgcn_raw_buffer_load_b64(wsr, o[c], r * (32 * ns0), 0));
+                        for (int r = 0; r < 4; ++r) d[c][r] = buf(wsr, o[c], sr[r]);
                 } else {  // with the row signs and the surplus columns
                     const unsigned long long mw = s_neg[R >> 2] >> ((R & 3) * 16);
 #pragma unroll
@@ -438,8 +475,7 @@ simplex_pend_kernel(KParams) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const int i = 16 * R + 4 * r + lr;
-                            const int off = i < m && j < n ? (i * n + j) * 8 : (int)0x80000000;
-                            d[c][r] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(asr, off, 0, 0));
+                            d[c][r] = buf(asr, i < m && j < n ? (unsigned)(i * n + j) * 8u : kPendOob, 0);
                         }
                     }
 #pragma unroll
@@ -461,7 +497,7 @@ simplex_pend_kernel(KParams) {
 #pragma unroll
                 for (int c = 0; c < TC; ++c) {
                     const int jt = cg * TC + c;  // slot tile
-                    const unsigned sm = jt * 16 < ldq ? s_slotmask[jt] : 0u;
+                    const unsigned sm = jt * 16 < ns ? s_slotmask[jt] : 0u;
                     if (__builtin_amdgcn_readfirstlane((int)(sm | rm))) {
                         const bool cb = (sm >> lc) & 1;
 #pragma unroll
@@ -469,19 +505,28 @@ simplex_pend_kernel(KParams) {
                     }
                 }
                 // four terms per step; the next step's factors are read ahead
-                const double* fa = F + (R * 16 + lc) * KS + lr;
-                const double* qb[TC];
+                // (the rows and slots past the end use the last one's)
+                auto term = [&](int off) __attribute__((always_inline)) {
+                    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(s_mem) + off);
+                };
+                const int half = (lr >> 1) * 16, odd = (lr & 1) * 8;
+                int fa = (f_off(min(R * 16 + lc, m - 1)) ^ half) + odd, qb[TC];
 #pragma unroll
-                for (int c = 0; c < TC; ++c) qb[c] = Q + (min((cg * TC + c) * 16, ldq - 16) + lc) * KS + lr;
-                double a = fa[0], b[TC];
+                for (int c = 0; c < TC; ++c)
+                    qb[c] = qbase + (f_off(min((cg * TC + c) * 16 + lc, ns - 1)) ^ half) + odd;
+                double a = term(fa), b[TC];
 #pragma unroll
-                for (int c = 0; c < TC; ++c) b[c] = qb[c][0];
+                for (int c = 0; c < TC; ++c) b[c] = term(qb[c]);
                 for (int g = 0; g < s; g += 4) {
-                    const int gn = min(g + 4, KP - 4);
-                    const double an = fa[gn];
+                    const bool more = g + 4 < s;
+                    fa += more ? m * 32 : 0;
+                    const double an = term(fa);
                     double bn[TC];
 #pragma unroll
-                    for (int c = 0; c < TC; ++c) bn[c] = qb[c][gn];
+                    for (int c = 0; c < TC; ++c) {
+                        qb[c] += more ? ns * 32 : 0;
+                        bn[c] = term(qb[c]);
+                    }
 #pragma unroll
                     for (int c = 0; c < TC; ++c) d[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[c], d[c], 0, 0, 0);
                     a = an;
@@ -494,8 +539,8 @@ simplex_pend_kernel(KParams) {
                     for (int r = 0; r < 4; ++r) {
                         const double w = d[c][r];
                         __builtin_amdgcn_raw_buffer_store_b64(
-                            __builtin_bit_cast(unsigned int __attribute__((ext_vector_type(2))), w), wsr, o[c],
-                            r * (32 * ns0), 0);
+                            __builtin_bit_cast(unsigned int __attribute__((ext_vector_type(2))), w), wsr, (int)o[c],
+                            sr[r], 0);
                     }
                 R += NW;
                 while (R >= nr) {
@@ -504,21 +549,10 @@ simplex_pend_kernel(KParams) {
                 }
             }
             __syncthreads();
-#pragma unroll
-            for (int q = 0; q < RT; ++q)
-                if (t + q * NT < ldf)
-                    for (int u = 0; u < s; ++u) F[(t + q * NT) * KS + u] = 0.0;
-#pragma unroll
-            for (int c = 0; c < CT; ++c)
-                if (t + c * NT < ldq)
-                    for (int u = 0; u < s; ++u) Q[(t + c * NT) * KS + u] = -0.0;
-            s = 0;
-            rb = sb = 0;
-            from_a = false;
-            lds_barrier();  // the factors are reset (others read them)
             // A slot that holds an artificial variable never enters again and
             // feeds no output: the last slot takes its place.  (The random
             // rule ranks the slots in slot order, so it keeps them.)
+            const int ns_was = ns;
             while (rule != 1 && ns > n) {
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
@@ -537,31 +571,43 @@ simplex_pend_kernel(KParams) {
                 const int from = ns - 1;
                 const bool gone = (s_dead[from >> 6] >> (from & 63)) & 1ull;
                 if (!gone) {
-#pragma unroll
-                    for (int q = 0; q < RT; ++q)
-                        if (t + q * NT < m) T[at(t + q * NT, to)] = T[at(t + q * NT, from)];
+                    if (rowt) T[(row_part(t) + slot_part(to)) >> 3] = T[(row_part(t) + slot_part(from)) >> 3];
 #pragma unroll
                     for (int c = 0; c < CT; ++c)
                         if (t + c * NT == from) {
-                            rec1[0].v0 = dO[c];
-                            rec1[0].v1 = dW[c];
-                            rec1[0].aux = cv[c];
+                            rec1[0].v0 = dP[c];
+                            rec1[0].v1 = dS[c];
+                            rec1[0].pk = cv[c];
                         }
                 }
                 __syncthreads();
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
                     if (!gone && t + c * NT == to) {
-                        dO[c] = rec1[0].v0;
-                        dW[c] = rec1[0].v1;
-                        cv[c] = rec1[0].aux;
+                        dP[c] = rec1[0].v0;
+                        dS[c] = rec1[0].v1;
+                        cv[c] = rec1[0].pk;
                     }
-                    cv[c] = t + c * NT == from ? ID_NONE : cv[c];
+                    if (t + c * NT == from) {
+                        dP[c] = dS[c] = ninf;
+                        cv[c] = ID_NONE;
+                    }
                 }
                 --ns;
                 lds_barrier();  // rec1 and s_dead are written again
             }
-            lds_barrier();
+            // clean factors; with fewer slots, room for more pivots
+            if (ns != ns_was) layout();
+            clear_factors(ns != ns_was ? KP : s);
+            s = 0;
+            rb = false;
+            sb = 0;
+            from_a = false;
+            ro = rowt ? (unsigned)row_part(t) : kPendOob;
+            slot_factors();
+#pragma unroll
+            for (int c = 0; c < CT; ++c) so[c] = t + c * NT < ns ? (unsigned)slot_part(t + c * NT) : kPendOob;
+            lds_barrier();  // the factors are clean before anyone reads them
         };
         BLP_T(t_load1);
         BLP_TACC(TM_LOAD, t_load0, t_load1);
@@ -577,47 +623,38 @@ simplex_pend_kernel(KParams) {
             }
             BLP_T(t_p0b);
             BLP_TACC(TM_RTEST, t_p0, t_p0b);
-            int e, e_id, l = -1, lv = ID_NONE, idx, th;
-            unsigned tl;
-            double fO, fW;
+            int e, e_id, l, lv;
+            double fP, fS;
             bool col_new;
             if (mode == 3) {
                 // the first row still holding an artificial variable
-                int mine = RT * NT;
-#pragma unroll
-                for (int q = RT - 1; q >= 0; --q)
-                    if (t + q * NT < m && t + q * NT >= drive_r && bs[q] >= id_lim && !((dead >> q) & 1u))
-                        mine = t + q * NT;
-                mine = wave_min_i32(mine);
-                if (lane == 0) rec1[wave].hi = -mine;
-                if (__ballot(nf)) nf_any = true;
-                nf = false;
-                if (lane == 0) {
-                    rec1[wave].lo = 0;
-                    rec1[wave].pk = 0;
-                    rec1[wave].nonfinite = nf_any;
-                }
+                const int mine = wave_min_i32(live && t >= drive_r && bs >= id_lim ? t : NT);
+                if (lane == 0) rec1[wave] = {-mine, 0u, 0, nfm ? 2 : 0};
                 __syncthreads();
-                bool any;
-                pend_best<NW>(rec1, lane, th, tl, idx, any);
-                const int r0 = -th;
+                int r0 = NT;
+                bool any = false;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    r0 = min(r0, -rec1[w].hi);
+                    any |= (rec1[w].flags & 2) != 0;
+                }
+                r0 = __builtin_amdgcn_readfirstlane(r0);
+                nf_any = __builtin_amdgcn_readfirstlane((int)any) != 0;
+                nfm = 0;
                 __syncthreads();  // rec1 is written again below
-                nf_any = any;
-                if (any) continue;  // flush first
-                if (r0 >= RT * NT) {
+                if (nf_any) continue;  // flush first
+                if (r0 >= NT) {  // phase 2: the objective prices
                     mode = 2;
                     degen = 0;
+                    zP = zS;
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) dP[c] = dS[c];
                     continue;
                 }
                 drive_r = r0 + 1;
-#pragma unroll
-                for (int q = 0; q < RT; ++q)
-                    if (t + q * NT == r0) {
-                        rec2[0].aux = (rb >> q) & 1u;
-                        rec2[0].pk = bs[q];
-                    }
+                if (t == r0) rec2[0] = {0, 0u, bs, rb ? 1 : 0};
                 __syncthreads();
-                const bool row_new = __builtin_amdgcn_readfirstlane(rec2[0].aux) != 0;
+                const bool row_new = __builtin_amdgcn_readfirstlane(rec2[0].flags) != 0;
                 lv = __builtin_amdgcn_readfirstlane(rec2[0].pk);
                 // the lowest-id non-artificial column with a usable entry enters
                 double x[CT];
@@ -627,71 +664,71 @@ simplex_pend_kernel(KParams) {
                 for (int c = 0; c < CT; ++c)
                     if (t + c * NT < ns && cv[c] < id_lim && fabs(x[c]) > eps_piv) pk = min(pk, pack_id(cv[c], t + c * NT));
                 pk = wave_min_i32(pk);
-                if (lane == 0) {
-                    rec1[wave].hi = pk == PACK_NONE ? (int)0x80000001 : -(pk >> 16);
-                    rec1[wave].lo = 0;
-                    rec1[wave].pk = pk;
-                    rec1[wave].nonfinite = 0;
-                }
+                if (lane == 0) rec1[wave] = {0, 0u, pk, 0};
 #pragma unroll
                 for (int c = 0; c < CT; ++c)
                     if (pk != PACK_NONE && t + c * NT == unpack_pos(pk)) {
-                        rec1[wave].v0 = dO[c];
-                        rec1[wave].v1 = dW[c];
-                        rec1[wave].aux = (sb >> c) & 1u;
+                        rec1[wave].flags = (sb >> c) & 1u;
+                        rec1[wave].v0 = dP[c];
+                        rec1[wave].v1 = dS[c];
                     }
                 __syncthreads();
-                pk = pend_best<NW>(rec1, lane, th, tl, idx, any);
-                if (pk == PACK_NONE) {  // redundant row
 #pragma unroll
-                    for (int q = 0; q < RT; ++q) dead |= (t + q * NT == r0 ? 1u : 0u) << q;
+                for (int w = 0; w < NW; ++w) pk = min(pk, rec1[w].pk);
+                pk = __builtin_amdgcn_readfirstlane(pk);
+                if (pk == PACK_NONE) {  // redundant row
+                    live = live && t != r0;
                     __syncthreads();
                     continue;
                 }
                 l = r0;
                 e = unpack_pos(pk);
                 e_id = unpack_id(pk);
-                fO = rec1[idx].v0;
-                fW = rec1[idx].v1;
-                col_new = __builtin_amdgcn_readfirstlane(rec1[idx].aux) != 0;
+                const PendRec& r = rec1[(e >> 6) & (NW - 1)];
+                fP = r.v0;
+                fS = r.v1;
+                col_new = __builtin_amdgcn_readfirstlane(r.flags) != 0;
             } else {
                 // Step 1: this wave's best slot
-                double bk = -__builtin_inf();
-                int bid = ID_NONE, bpos = -1;
-                const bool rpc = rule == 1 && degen < bland_after;
+                double key = dP[0], ds = dS[0];
+                int pk;
+                unsigned bit = sb & 1u;
+                bool ok = key > eps_price;
                 const bool bland = degen >= bland_after;
-                unsigned elig = 0;
-#pragma unroll
-                for (int c = 0; c < CT; ++c) {
-                    const int j = t + c * NT;
-                    const double d = mode == 1 ? dW[c] : dO[c];
-                    const bool ok = (j < ns) & (cv[c] < id_lim) & (d > eps_price);
-                    const double key = bland ? 0.0 : d;
-                    const bool take = ok & ((key > bk) | ((key == bk) & (cv[c] < bid)));
-                    bk = take ? key : bk;
-                    bid = take ? cv[c] : bid;
-                    bpos = take ? j : bpos;
-                    elig |= (ok ? 1u : 0u) << c;
+                if (ns > NT) {
+                    const double d1 = dP[1];
+                    const bool ok1 = d1 > eps_price;
+                    const bool less = bland ? cv[0] < cv[1] : (key > d1) | ((key == d1) & (cv[0] < cv[1]));
+                    const bool take = ok1 & !(ok & less);
+                    key = take ? d1 : key;
+                    ds = take ? dS[1] : ds;
+                    bit = take ? (sb >> 1) & 1u : bit;
+                    ok |= ok1;
+                    pk = take ? (cv[1] << 16) | (t + NT) : (cv[0] << 16) | t;
+                } else {
+                    pk = (cv[0] << 16) | t;
                 }
-                if (rpc) {
+                double ck = ok ? (bland ? 0.0 : key) : ninf;
+                pk = ok ? pk : PACK_NONE;
+                if (rule == 1 && !bland) {
                     // Sec. 4.2's random positive coefficient: the target-th
                     // eligible slot in slot order
                     __syncthreads();  // s_dead is free
+                    unsigned long long em[CT];
 #pragma unroll
                     for (int c = 0; c < CT; ++c) {
-                        const unsigned long long em = __ballot((elig >> c) & 1u);
-                        if (lane == 0) s_dead[c * NW + wave] = em;
+                        em[c] = __ballot(t + c * NT < ns && cv[c] < id_lim && dP[c] > eps_price);
+                        if (lane == 0) s_dead[c * NW + wave] = em[c];
                     }
                     __syncthreads();
                     int total = 0, rank[CT];
 #pragma unroll
                     for (int w = 0; w < CT * NW; ++w) {
-                        const unsigned long long em = s_dead[w];
-                        if ((w & (NW - 1)) == wave) rank[w / NW] = total + __popcll(em & ((1ull << lane) - 1ull));
-                        total += __popcll(em);
+                        if ((w & (NW - 1)) == wave) rank[w / NW] = total + __popcll(em[w / NW] & ((1ull << lane) - 1ull));
+                        total += __popcll(s_dead[w]);
                     }
-                    bk = -__builtin_inf();
-                    bid = ID_NONE;
+                    ck = ninf;
+                    pk = PACK_NONE;
                     if (total > 0) {
                         uint32_t c4[4] = {(uint32_t)iters, (uint32_t)k, 0x52504321u, 0u};
                         const uint64_t seed = kparams().seed;
@@ -702,39 +739,34 @@ simplex_pend_kernel(KParams) {
                         if (target >= total) target = total - 1;
 #pragma unroll
                         for (int c = 0; c < CT; ++c)
-                            if (((elig >> c) & 1u) && rank[c] == target) {
-                                bk = 1.0;
-                                bid = cv[c];
-                                bpos = t + c * NT;
+                            if (((em[c] >> lane) & 1ull) && rank[c] == target) {
+                                ck = 1.0;
+                                pk = pack_id(cv[c], t + c * NT);
+                                key = dP[c];
+                                ds = dS[c];
+                                bit = (sb >> c) & 1u;
                             }
                     }
                 }
-                const long long kb = __double_as_longlong(bk);
+                const long long kb = __double_as_longlong(ck);
                 int wh;
                 unsigned wl;
-                int pk = wave_argmax_i64((int)(kb >> 32), (unsigned)kb, pack_id(bid, bpos), wh, wl);
-                bool any = __ballot(nf) != 0;
-                nf = false;
+                pk = wave_argmax_i64((int)(kb >> 32), (unsigned)kb, pk, wh, wl);
+                unsigned flags = nfm ? 2u : 0u;
+                nfm = 0;
                 if constexpr (NW > 1) {
-                    PendRec& r = rec1[wave];
-                    if (lane == 0) {
-                        r.hi = wh;
-                        r.lo = wl;
-                        r.pk = pk;
-                        r.nonfinite = any;
+                    if (lane == (pk == PACK_NONE ? 0 : pk & 63)) {
+                        PendRec& r = rec1[wave];
+                        *reinterpret_cast<int4*>(&r) = make_int4(wh, (int)wl, pk, (int)(flags | bit));
+                        r.v0 = key;
+                        r.v1 = ds;
                     }
-                    const int pos = unpack_pos(pk);
-#pragma unroll
-                    for (int c = 0; c < CT; ++c)
-                        if (t + c * NT == pos) {
-                            r.aux = (sb >> c) & 1u;
-                            r.v0 = dO[c];
-                            r.v1 = dW[c];
-                        }
+                    if (NW == 2)
+                        flags = (flags & 2u) | ((unsigned)__builtin_amdgcn_readlane((int)bit, pk & 63) & 1u);
                     lds_barrier();
-                    pk = pend_best<NW>(rec1, lane, th, tl, idx, any);
+                    pk = pend_best<NW>(rec1, lane, wave, wh, wl, pk, flags);
                 }
-                if (any) {  // a non-finite pivot entry: flush first, then price again
+                if (flags & 2u) {  // a non-finite pivot entry: flush first, then price again
                     nf_any = true;
                     if (NW > 1) __syncthreads();  // rec1 is written again
                     continue;
@@ -744,7 +776,7 @@ simplex_pend_kernel(KParams) {
                         st = ST_OPTIMAL;
                         break;
                     }
-                    if (zW > kparams().eps_feas * (1.0 + w0)) {
+                    if (zP > kparams().eps_feas * (1.0 + w0)) {
                         st = ST_INFEASIBLE;
                         break;
                     }
@@ -760,112 +792,102 @@ simplex_pend_kernel(KParams) {
                 e = unpack_pos(pk);
                 e_id = unpack_id(pk);
                 if constexpr (NW > 1) {
-                    fO = rec1[idx].v0;
-                    fW = rec1[idx].v1;
-                    col_new = __builtin_amdgcn_readfirstlane(rec1[idx].aux) != 0;
+                    const PendRec& r = rec1[(e >> 6) & (NW - 1)];
+                    fP = r.v0;
+                    fS = r.v1;
+                    col_new = flags & 1u;
                 } else {
-                    fO = mirror_at(dO, e);
-                    fW = mirror_at(dW, e);
-                    col_new = ((unsigned)__builtin_amdgcn_readlane((int)sb, e & 63) >> (e >> 6)) & 1u;
+                    fP = lane_f64(key, e & 63);
+                    fS = lane_f64(ds, e & 63);
+                    col_new = __builtin_amdgcn_readlane((int)bit, e & 63) & 1;
                 }
             }
-            // entering column
+            // entering column: this thread's row
             BLP_T(t_p1);
-            double f[RT];
-            column(e, col_new, f);
-#pragma unroll
-            for (int q = 0; q < RT; ++q) nf |= !isfinite(f[q]);
+            double f = 0.0;
+            if (!col_new) {
+                if (!from_a) {
+                    f = buf(wsr, ro, slot_part(e));
+                } else if (e < n) {
+                    f = buf(asr, ro, e * 8);
+                    f = __hiloint2double(__double2hiint(f) ^ (int)neg, __double2loint(f));
+                } else {
+                    f = s_art[e - n] == t && !rb ? -1.0 : 0.0;
+                }
+            }
+            // the last pivot row's older factors: nobody else reads them now
+            if (zl >= 0 && wave == zl >> 6 && lane < s - 1) cell(0, m, zl, lane) = 0.0;
+            int fb = qbase + f_off(e), fa = fad;
+            for (int kb = 0; kb < s; kb += 4, fa += m * 32, fb += ns * 32)
+                f = fma4(pair(fa), pair(fa ^ 16), pair(fb), pair(fb ^ 16), f);
+            f = rowt ? f : 0.0;
+            nfm |= __ballot(!isfinite(f));
             BLP_T(t_p2);
-            // Step 2: one IEEE reciprocal y = 1 / f per row gives the ratio
-            // (rhs / f by the corrected product of div_rn_fast) and, for the
-            // winner, the reciprocal that divides the pivot row
-            double rmin = 1.0, pe, y, pr;
+            // Step 2: one IEEE reciprocal y = 1 / f gives the ratio (rhs / f by
+            // the corrected product of div_rn_fast) and, for the winner, the
+            // reciprocal that divides the pivot row
+            double pe, y, pr;
             bool row_new;
             if (mode != 3) {
-                double yv[RT], qt[RT];
-                bool cand[RT], slow = false;
-#pragma unroll
-                for (int q = 0; q < RT; ++q) {
-                    cand[q] = (t + q * NT < m) & !((dead >> q) & 1u) & (f[q] > eps_piv);
-                    const double a = cand[q] ? f[q] : 1.0;
-                    yv[q] = 1.0 / a;
-                    __asm__("" : "+v"(yv[q]));
-                    bool ok;
-                    qt[q] = div_rn_fast(bR[q], a, yv[q], (a >= 0x1p-500) & (a <= 0x1p500), ok);
-                    slow |= cand[q] & !ok;
-                }
-                if (__ballot(slow)) {
-#pragma unroll
-                    for (int q = 0; q < RT; ++q) qt[q] = bR[q] / (cand[q] ? f[q] : 1.0);
-                }
-                double bk = -__builtin_inf();
-                int bid = ID_NONE, bpos = -1;
-#pragma unroll
-                for (int q = 0; q < RT; ++q) {
-                    const double key = bR[q] <= 0.0 ? -0.0 : -qt[q];
-                    const bool take = cand[q] & ((key > bk) | ((key == bk) & (bs[q] < bid)));
-                    bk = take ? key : bk;
-                    bid = take ? bs[q] : bid;
-                    bpos = take ? t + q * NT : bpos;
-                }
-                const long long kb = __double_as_longlong(-bk);
+                const bool cand = live & (f > eps_piv);
+                const double a = cand ? f : 1.0;
+                double yv = 1.0 / a;
+                __asm__("" : "+v"(yv));
+                bool ok;
+                double qt = div_rn_fast(bR, a, yv, (a >= 0x1p-500) & (a <= 0x1p500), ok);
+                if (__ballot(cand & !ok)) qt = plain_div(bR, a);
+                const double ratio = bR <= 0.0 ? 0.0 : qt;
+                const bool take = cand & (ratio <= __builtin_inf());  // (a NaN ratio is no candidate)
+                const long long kb = __double_as_longlong(take ? ratio : __builtin_inf());
                 int wh;
                 unsigned wl;
-                int pk = wave_argmax_i64(~(int)(kb >> 32), ~(unsigned)kb, pack_id(bid, bpos), wh, wl);
+                int pk =
+                    wave_argmax_i64(~(int)(kb >> 32), ~(unsigned)kb, take ? (bs << 16) | t : PACK_NONE, wh, wl);
+                unsigned flags = 0;
                 if constexpr (NW > 1) {
-                    PendRec& r = rec2[wave];
-                    if (lane == 0) {
-                        r.hi = wh;
-                        r.lo = wl;
-                        r.pk = pk;
-                        r.nonfinite = 0;
+                    if (lane == (pk == PACK_NONE ? 0 : pk & 63)) {
+                        PendRec& r = rec2[wave];
+                        *reinterpret_cast<int4*>(&r) = make_int4(wh, (int)wl, pk, rb ? 1 : 0);
+                        r.v0 = f;
+                        r.v1 = yv;
+                        r.v2 = qt;
                     }
-                    const int pos = unpack_pos(pk);
-#pragma unroll
-                    for (int q = 0; q < RT; ++q)
-                        if (t + q * NT == pos) {
-                            r.aux = (rb >> q) & 1u;
-                            r.v0 = f[q];
-                            r.v1 = yv[q];
-                            r.v2 = qt[q];
-                        }
+                    if (NW == 2) flags = (__ballot(rb) >> (pk & 63)) & 1ull;
                     lds_barrier();
-                    bool any;
-                    pk = pend_best<NW>(rec2, lane, wh, wl, idx, any);
+                    pk = pend_best<NW>(rec2, lane, wave, wh, wl, pk, flags);
                 }
                 if (pk == PACK_NONE) {
                     st = mode == 2 ? ST_UNBOUNDED : ST_NUMERICAL;
                     break;
                 }
-                rmin = __longlong_as_double((long long)(((unsigned long long)(unsigned)~wh << 32) | (unsigned)~wl));
                 l = unpack_pos(pk);
                 lv = unpack_id(pk);
                 if constexpr (NW > 1) {
-                    pe = rec2[idx].v0;
-                    y = rec2[idx].v1;
-                    pr = rec2[idx].v2;
-                    row_new = __builtin_amdgcn_readfirstlane(rec2[idx].aux) != 0;
+                    const PendRec& r = rec2[l >> 6];
+                    pe = r.v0;
+                    y = r.v1;
+                    pr = r.v2;
+                    row_new = flags & 1u;
                 } else {
-                    pe = mirror_at(f, l);
-                    y = mirror_at(yv, l);
-                    pr = mirror_at(qt, l);
-                    row_new = ((unsigned)__builtin_amdgcn_readlane((int)rb, l & 63) >> (l >> 6)) & 1u;
+                    pe = lane_f64(f, l);
+                    y = lane_f64(yv, l);
+                    pr = lane_f64(qt, l);
+                    row_new = (__ballot(rb) >> l) & 1ull;
                 }
+                degen = pr <= 0.0 ? degen + 1 : 0;  // a zero step
             } else {
                 __syncthreads();  // rec2[0] has been read by everyone
-#pragma unroll
-                for (int q = 0; q < RT; ++q)
-                    if (t + q * NT == l) {
-                        rec2[0].v0 = f[q];
-                        rec2[0].v1 = 1.0 / f[q];
-                        rec2[0].v2 = bR[q] / f[q];
-                        rec2[0].aux = (rb >> q) & 1u;
-                    }
+                if (t == l) {
+                    rec2[0].flags = rb ? 1 : 0;
+                    rec2[0].v0 = f;
+                    rec2[0].v1 = 1.0 / f;
+                    rec2[0].v2 = bR / f;
+                }
                 __syncthreads();
                 pe = rec2[0].v0;
                 y = rec2[0].v1;
                 pr = rec2[0].v2;
-                row_new = __builtin_amdgcn_readfirstlane(rec2[0].aux) != 0;
+                row_new = __builtin_amdgcn_readfirstlane(rec2[0].flags) != 0;
             }
             BLP_T(t_p3);
             // Step 3: the new pivot row, the mirrors, and the pending factors
@@ -874,51 +896,42 @@ simplex_pend_kernel(KParams) {
             const double ape = fabs(pe);
             const bool pe_ok = ape >= 0x1p-500 && ape <= 0x1p500;
             // slot e's older factors (its column has been read by everyone)
-            if (wave == ((e >> 6) & (NW - 1)) && lane < s) Q[e * KS + lane] = -0.0;
-            double p[CT];
-            bool slow = false;
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                x[c] = t + c * NT == e ? 1.0 : x[c];
-                bool ok;
-                p[c] = div_rn_fast(x[c], pe, y, pe_ok, ok);
-                slow |= !ok;
-            }
-            if (__ballot(slow)) {  // extreme magnitudes only: the plain division
-#pragma unroll
-                for (int c = 0; c < CT; ++c) p[c] = x[c] / pe;
-            }
-            const int th2 = here(t);
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                if (c > 0 && ns <= c * NT) break;
-                const int j = th2 + c * NT;
+            if (wave == ((e >> 6) & (NW - 1)) && lane < s) cell(qbase, ns, e, lane) = -0.0;
+            auto new_slot = [&](auto cc) __attribute__((always_inline)) {
+                constexpr int c = decltype(cc)::value;
+                const int j = t + c * NT;
                 const bool ent = j == e;
-                dO[c] = __builtin_fma(-fO, p[c], ent ? 0.0 : dO[c]);
-                if (mode != 2) dW[c] = __builtin_fma(-fW, p[c], ent ? 0.0 : dW[c]);
+                const double xv = ent ? 1.0 : x[c];
+                bool ok;
+                double p = div_rn_fast(xv, pe, y, pe_ok, ok);
+                if (__ballot(!ok)) p = plain_div(xv, pe);  // extreme magnitudes only: the plain division
+                dP[c] = __builtin_fma(-fP, p, ent ? 0.0 : dP[c]);
+                if (mode != 2) dS[c] = __builtin_fma(-fS, p, ent ? 0.0 : dS[c]);
                 cv[c] = ent ? lv : cv[c];
-                sb |= (ent ? 1u : 0u) << c;
-                nf |= !isfinite(p[c]);
-                if (j < ldq) Q[j * KS + s] = p[c];
-            }
-            zO = __builtin_fma(-fO, pr, zO);
-            zW = __builtin_fma(-fW, pr, zW);
-#pragma unroll
-            for (int q = 0; q < RT; ++q) {
-                const int i = th2 + q * NT;
-                const bool piv = i == l;
-                bR[q] = piv ? pr : __builtin_fma(-f[q], pr, bR[q]);
-                bs[q] = piv ? e_id : bs[q];
-                rb |= (piv ? 1u : 0u) << q;
-                if (i < ldf) F[i * KS + s] = piv ? 1.0 : (i < m ? -f[q] : 0.0);
-            }
+                so[c] = ent ? kPendOob : so[c];
+                sb |= ent ? 1u << c : 0u;
+                if (lv >= id_lim) {  // an artificial variable never enters again
+                    dP[c] = ent ? ninf : dP[c];
+                    dS[c] = ent ? ninf : dS[c];
+                }
+                nfm |= __ballot(!isfinite(p));
+                if (j < ns) cell(qbase, ns, j, s) = p;
+            };
+            new_slot(std::integral_constant<int, 0>{});
+            if (ns > NT) new_slot(std::integral_constant<int, 1>{});
+            zP = __builtin_fma(-fP, pr, zP);
+            zS = __builtin_fma(-fS, pr, zS);
+            const bool piv = t == l;
+            bR = piv ? pr : __builtin_fma(-f, pr, bR);
+            bs = piv ? e_id : bs;
+            ro = piv ? kPendOob : ro;
+            neg = piv ? 0u : neg;
+            rb |= piv;
+            if (rowt) cell(0, m, t, s) = piv ? 1.0 : -f;
             zl = l;
             ++s;
             ++iters;
-            if (mode != 3)
-                degen = rmin == 0.0 ? degen + 1 : 0;
-            else
-                __syncthreads();  // rec1 and rec2 are written again
+            if (mode == 3) __syncthreads();  // rec1 and rec2 are written again
             BLP_T(t_p4);
             BLP_TACC(TM_PRICE, t_p0b, t_p1);
             BLP_TACC(TM_PUBCOL, t_p1, t_p2);
@@ -934,28 +947,26 @@ simplex_pend_kernel(KParams) {
         const KParams PX = kparams();
         const LpRef LX = lp_ref(PX, k);
         const int64_t sense_off = lp_in(PX, LX).row_off;
-        const double z = -zO;
+        const double z = mode == 2 ? -zP : -zS;
         const int sto = st == ST_OPTIMAL && !isfinite(z) ? ST_NUMERICAL : st;
         const bool nan_out = sto == ST_NUMERICAL;
         const double qnan = __builtin_nan("");
         auto put_y = [&](int i, double d) __attribute__((always_inline)) {
             PX.y[LX.row_off + i] = nan_out ? qnan : (PX.sense[sense_off + i] != 0 ? d : -d);
         };
-#pragma unroll
-        for (int q = 0; q < RT; ++q)
-            if (t + q * NT < m) {
-                if (bs[q] < n)
-                    PX.x[LX.col_off + bs[q]] = nan_out ? qnan : bR[q];
-                else if (bs[q] < n + m)
-                    put_y(bs[q] - n, 0.0);
-            }
+        if (rowt) {
+            if (bs < n)
+                PX.x[LX.col_off + bs] = nan_out ? qnan : bR;
+            else if (bs < n + m)
+                put_y(bs - n, 0.0);
+        }
 #pragma unroll
         for (int c = 0; c < CT; ++c)
             if (t + c * NT < ns) {
                 if (cv[c] < n)
                     PX.x[LX.col_off + cv[c]] = nan_out ? qnan : 0.0;
                 else if (cv[c] < n + m)
-                    put_y(cv[c] - n, dO[c]);
+                    put_y(cv[c] - n, mode == 2 ? dP[c] : dS[c]);
             }
         if (t == 0) {
             PX.status[k] = sto;
@@ -979,14 +990,14 @@ simplex_pend_kernel(KParams) {
 template <int I>
 static hipError_t launch_pend_i(const KParams& P, int grid, size_t lds_bytes, hipStream_t s) {
     constexpr PendTile T = kPendTiles[I];
-    hipLaunchKernelGGL((simplex_pend_kernel<T.waves, T.rows_per, T.slots_per, T.tiles, T.wpe>), dim3(grid), dim3(T.waves * 64), lds_bytes,
+    hipLaunchKernelGGL((simplex_pend_kernel<T.waves, T.tiles, T.wpe>), dim3(grid), dim3(T.waves * 64), lds_bytes,
                        s, P);
     return hipGetLastError();
 }
 template <int I>
 static const void* pend_ptr_i() {
     constexpr PendTile T = kPendTiles[I];
-    return reinterpret_cast<const void*>(&simplex_pend_kernel<T.waves, T.rows_per, T.slots_per, T.tiles, T.wpe>);
+    return reinterpret_cast<const void*>(&simplex_pend_kernel<T.waves, T.tiles, T.wpe>);
 }
 static_assert(kPendRows == kPendTiles[kPendTileCount - 1].rows() && kPendSlots == kPendTiles[kPendTileCount - 1].slots(),
               "pend_shape() is what the largest tile holds");

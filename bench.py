@@ -29,7 +29,7 @@ PEAK_HBM_GBS = 8000.0     # MI355X HBM3E
 PEAK_LDS_GBS = 78643.2    # 256 CUs x 128 B/clk x 2.4 GHz
 METRIC = "LPs/sec per size class, batched persistent vs one-LP-per-launch, obj relerr\u22641e-9"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_dominant_kernel__type1_m100_n100_K50000.json")
-KERNEL_SOURCES = ["paper_1609_08114_amd/csrc/simplex_reg.hip", "paper_1609_08114_amd/csrc/simplex_blk.hpp",
+KERNEL_SOURCES = ["paper_1609_08114_amd/csrc/simplex_pend.hip", "paper_1609_08114_amd/csrc/simplex_reg.hip", "paper_1609_08114_amd/csrc/simplex_blk.hpp",
                   "paper_1609_08114_amd/csrc/simplex_cols.hpp", "paper_1609_08114_amd/csrc/simplex_lane.hpp",
                   "paper_1609_08114_amd/csrc/simplex_lane.hip",
                   "paper_1609_08114_amd/csrc/simplex_common.hpp", "paper_1609_08114_amd/csrc/blp_kernels.hpp",
@@ -113,13 +113,12 @@ def _timer_child(K: int) -> None:
     s.close()
 
 
-def phase_timers(K: int) -> dict | None:
+def phase_timers(K: int, kernel: str) -> dict | None:
     """Per-phase cycles of the headline solve from the phase-timer build (a
-    child process), or None if that build is absent.  For the column-split
-    kernel the four pivot phases are: candidate (the wave's Step 1, column
-    publication and Step 2), exchange (candidate record, the barrier, the
-    winner), pivot row (publication and division) and update (mirrors and
-    the rank-1 update of the tile)."""
+    child process), or None if that build is absent: of the pending-pivot
+    kernel pricing, the entering column, the ratio test, the leaving row (with
+    the mirrors and the new factors) and the flush, spread over the pivots;
+    of the block tiles candidate, exchange, pivot row and update."""
     import re
     import subprocess
     if not os.path.exists(TIMER_LIB):
@@ -128,19 +127,23 @@ def phase_timers(K: int) -> dict | None:
     r = subprocess.run([sys.executable, "-c", f"import bench; bench._timer_child({K})"], cwd=ROOT, env=env,
                        capture_output=True, text=True, timeout=600)
     m = re.search(r"\[blp timers\] LPs (\d+) pivots (\d+) \| cycles per LP: load ([\d.]+) extract ([\d.]+) \| "
-                  r"per pivot: price ([\d.]+) pubcol ([\d.]+) ratio ([\d.]+) pivot ([\d.]+)", r.stderr)
+                  r"per pivot: price ([\d.]+) pubcol ([\d.]+) ratio ([\d.]+) pivot ([\d.]+) \| ratio test ([\d.]+)",
+                  r.stderr)
     if r.returncode != 0 or not m:
         log(f"phase timers: no counters (rc {r.returncode}): {r.stderr[-400:]}")
         return None
     lps, piv = int(m.group(1)), int(m.group(2))
-    load, extract, cand, exch, prow, upd = (float(m.group(i)) for i in range(3, 9))
-    per_pivot = cand + exch + prow + upd
+    load, extract, *phase = (float(m.group(i)) for i in range(3, 10))
+    if kernel.startswith("p"):
+        keys = ["price", "column", "ratio", "row", "flush"]
+    else:
+        keys, phase = ["candidate", "exchange", "pivot_row", "update"], phase[:4]
+    per_pivot = sum(phase)
     per_lp = load + extract + per_pivot * piv / max(lps, 1)
     return {"lps": lps, "pivots": piv, "unit": "cycles of one wave (s_memtime), per LP and per pivot",
             "per_lp": {"load": round(load), "extract": round(extract)},
-            "per_pivot": {"candidate": round(cand), "exchange": round(exch), "pivot_row": round(prow),
-                          "update": round(upd)},
-            "update_share_of_pivot": round(upd / per_pivot, 4) if per_pivot > 0 else None,
+            "per_pivot": {k: round(v) for k, v in zip(keys, phase)},
+            "update_share_of_pivot": round(phase[-1] / per_pivot, 4) if per_pivot > 0 else None,
             "pivot_loop_share_of_lp": round(per_pivot * piv / max(lps, 1) / per_lp, 4) if per_lp > 0 else None}
 
 
@@ -222,10 +225,11 @@ def main():
     dom = int(np.argmax(kms))
     dom_ms = float(kms[dom])
     m = n = 100
-    # Work per pivot as executed: the kernel stores the condensed tableau,
-    # the n nonbasic columns and the rhs of the m constraint rows and the
-    # objective row, (m + 1)(n + 1) entries, one FMA each (the basic columns
-    # of the full tableau of Sec. 3.1 are unit vectors and are not stored).
+    # Work per pivot: the condensed tableau, the n nonbasic columns and the rhs
+    # of the m constraint rows and the objective row, (m + 1)(n + 1) entries,
+    # one FMA each (the basic columns of the full tableau of Sec. 3.1 are unit
+    # vectors and are not stored).  The pending-pivot kernel makes fewer: an LP
+    # that ends before a flush never updates its whole tableau.
     # The full tableau, (m + 1)(n + m + 1) entries, is reported as context.
     executed = float(iters.sum()) * 2.0 * (m + 1) * (n + 1)
     full = float(iters.sum()) * 2.0 * (m + 1) * (n + m + 1)
@@ -247,7 +251,7 @@ def main():
                 "hbm_frac_of_input_read": round(input_bytes / (dom_ms / 1e3) / 1e9 / PEAK_HBM_GBS, 4)}
 
     # per-phase cycles of the same solve (phase-timer build, child process)
-    timers = phase_timers(K)
+    timers = phase_timers(K, names[dom])
     if timers:
         roofline["phase_cycles"] = timers
         log(f"phase timers: {timers}")
@@ -700,21 +704,20 @@ def bench_classes(blp, torch, lpgen, plan=None) -> dict:
                           "note": "batch larger than the 256 MB last-level cache; bytes are the algorithmic "
                                   "stream (HBM counters of the same kernels in profiles/)"})
         if cfg == 3:
-            # the streaming kernel reads and writes each stored tableau entry
-            # once per pivot (ldk x (n + n_art + 1) in phase 1, the artificial
-            # columns skipped in phase 2); part of it hits the L2 and the
-            # last-level cache, so this is a tableau stream, not HBM traffic
+            # one FMA per stored tableau entry and pivot (n + n_art + 1
+            # columns, the phase-1 width, an upper bound)
             m, n = int(hb.m[0]), int(hb.n[0])
             sense = hb.sense.reshape(n_batch, m) != 0
             b = hb.b.reshape(n_batch, m)
             nart = ((np.where(sense, -b, b)) < 0).sum(axis=1)
             it = out["iters"][:n_batch].cpu().numpy().astype(np.float64)
-            gms = float(kms[len(blp.variants())])
-            stored = float((it * 16.0 * (m + 2) * (n + nart + 1)).sum())
-            entry.update({"streaming_kernel_ms": round(gms, 3), "pivots_per_lp": round(float(it.mean()), 1),
-                          "tableau_stream_GBps_l2_mall_hbm": round(stored / gms / 1e6, 1),
-                          "tableau_stream_note": "16 B per stored entry per pivot (phase-1 width, an upper "
-                                                 "bound); served by L2, the last-level cache and HBM"})
+            dom = int(np.argmax(kms[:len(blp.variants()) + 1]))
+            gms = float(kms[dom])
+            fma = float((it * 2.0 * (m + 1) * (n + nart + 1)).sum())
+            entry.update({"kernel": names[dom], "simplex_kernel_ms": round(gms, 3),
+                          "pivots_per_lp": round(float(it.mean()), 1),
+                          "update_tflops": round(fma / gms / 1e9, 3),
+                          "update_frac_of_fp64_peak": round(fma / gms / 1e9 / PEAK_FP64_TFLOPS, 4)})
         if n_single is None or n_single > 0:
             S = n_batch if n_single is None else n_single
             sub = db if S == n_batch else blp.DeviceBatch.from_host(

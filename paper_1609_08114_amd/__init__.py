@@ -299,6 +299,28 @@ class DeviceBatch:
                          _ptr(self.A), _ptr(self.b), _ptr(self.sense), _ptr(self.c), _ptr(self.l), _ptr(self.u))
 
 
+def _backward_fills(db: DeviceBatch, key: str, src) -> bool:
+    """Whether blp_backward writes every element of gradient `key` (the size
+    of batch array `src`): simplex LPs write dc, db and dA, hyperboxes dc, dl
+    and du, so the LPs have to be of that kind and lie end to end.  Then the
+    tensor needs no zeros first (a pass over 4 GB for 6 million boxes of 28:
+    2.92 -> 2.30 ms with their solve).  The offsets of a batch that is not
+    uniform are looked at (some 5 ns per LP) only where the zeros take longer:
+    from 4,096 elements per LP."""
+    K, box = db.count, key in ("dl", "du")
+    if K == 0 or (box and db.shared_box):
+        return False
+    if db.uniform:
+        m, n, kind = int(db.m[0]), int(db.n[0]), int(db.kind[0])
+        each = {"dc": n, "db": m, "dA": m * n, "dl": n, "du": n}[key]
+        return src.numel() == each * K and (key == "dc" or (kind == 1) == box)
+    if src.numel() < 4096 * K or (key != "dc" and not ((db.kind == 1) == box).all()):
+        return False
+    each = db.n if key in ("dc", "dl", "du") else db.m.astype(np.int64) * (db.n if key == "dA" else 1)
+    off = {"db": db.row_off, "dA": db.a_off}.get(key, db.col_off)
+    return bool(off[0] == 0 and off[-1] + each[-1] == src.numel() and (off[1:] - off[:-1] == each[:-1]).all())
+
+
 class Solver:
     """A handle plus device result tensors.  One per host thread."""
 
@@ -421,7 +443,12 @@ class Solver:
                 src = {"dc": db.c, "db": db.b, "dA": db.A, "dl": db.l, "du": db.u}[k]
                 if k in ("dl", "du") and src is not None and getattr(db, "shared_box", False):
                     src = src[:int(db.n[db.kind == 1][0])]
-                res[k] = None if src is None else torch.zeros_like(src)
+                if src is None:
+                    res[k] = None
+                elif _backward_fills(db, k, src):
+                    res[k] = torch.empty_like(src)
+                else:
+                    res[k] = torch.zeros_like(src)
         st = stream if stream is not None else torch.cuda.current_stream(dev)
         blp_backward(self.h, _ptr(g), _ptr(res.get("dc")), _ptr(res.get("db")), _ptr(res.get("dA")),
                      _ptr(res.get("dl")), _ptr(res.get("du")), st.cuda_stream)

@@ -187,6 +187,7 @@ simplex_blk_kernel(KParams P) {
     constexpr int ROW_OBJ = RP - 1, ROW_W = RP - 2, COL_RHS = CP - 1;
     constexpr int RS = (RP + 63) / 64, CS = (CP + 63) / 64;
     static_assert(GR * GC == NT && 64 % GC == 0 && RP >= 4 && CP >= 2 && RS <= 32, "bad block tile");
+    static_assert(!SH || (CP <= NT && RP == CP), "one objective coefficient per thread");
 
     // pivot column / pivot row, padded to whole waves so that every lane
     // reads its mirror entries without a bounds branch
@@ -195,9 +196,10 @@ simplex_blk_kernel(KParams P) {
     __shared__ int s_artrow[RP], s_rank[RP];
     __shared__ unsigned char s_flag[RP];
     __shared__ int s_k, s_nart, s_bad;
-    // shared-constraint mode: objective coefficients of the basis, per row
-    // group partial sums of the rebuilt objective row, the chunk being served
-    __shared__ double s_cb[SH ? RP : 1], s_part[SH ? GR * CP : 1];
+    // shared-constraint mode: objective coefficients of the basis (every wave
+    // its own copy), per row group partial sums of the rebuilt objective row,
+    // the chunk being served
+    __shared__ double s_cb[SH ? NW * RP : 1], s_part[SH ? GR * CP : 1];
     __shared__ int64_t s_cur, s_end;
     __shared__ int s_pending;      // SH: objective handed back to a cold start
     __shared__ double s_sim[3 * NW];  // SH: per-wave sums for the similarity test
@@ -431,7 +433,7 @@ simplex_blk_kernel(KParams P) {
         }
         if (bad) atomicOr(&s_bad, 1);
         lds_barrier();
-        if (s_bad) {
+        if (__builtin_amdgcn_readfirstlane(s_bad)) {
             write_numerical<NT>(P, L, k, t, ST_NUMERICAL);
             lds_barrier();
             continue;
@@ -451,7 +453,7 @@ simplex_blk_kernel(KParams P) {
             }
             if (badp) atomicOr(&s_bad, 1);
             lds_barrier();
-            if (!ok || s_bad) {
+            if (__builtin_amdgcn_readfirstlane(!ok || s_bad)) {
                 write_numerical<NT>(P, L, k, t, ST_INTERNAL);
                 lds_barrier();
                 continue;
@@ -465,17 +467,30 @@ simplex_blk_kernel(KParams P) {
         const int id_lim = n + m;
         int iters = 0, degen = 0, st = -1;
 
+        // SH: this thread's objective coefficient, and that of LP k + 1, which
+        // is usually the next (loaded while LP k is solved)
+        double c_own = 0.0, c_next = 0.0;
+        auto load_c = [&](int kk) __attribute__((always_inline)) {
+            return P.c[lp_ref(P, kk).col_off + min(t, n - 1)];
+        };
+        if constexpr (SH) {
+            c_own = t < n ? s_c[t] : 0.0;
+            c_next = load_c(min(k + 1, (int)P.count - 1));
+        }
+        const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+
         // Outputs of LP k straight from the mirrors (wave 0; the mirrors are
-        // identical in every wave).  Every structural and logical variable
+        // identical in every wave, so in shared-constraint mode, where this is
+        // a large part of an LP's time, the waves share the work).  Every structural and logical variable
         // sits in exactly one place, a row (basic: x = rhs, dual 0) or a
         // slot (nonbasic: x = 0, dual from the objective row), so x and y are
         // written by one scatter each, without LDS or barriers; the duals
         // take the same signs as the oracle's (-d for "<=" rows, also on a
         // zero d).  Only s_flag is read, which no other wave writes before
         // the next pop's barrier.
-        auto extract = [&]() __attribute__((always_inline)) {
+        auto extract = [&](int k) __attribute__((always_inline)) {
             BLP_T(t_x0);
-            if (t < 64) {
+            if (SH || t < 64) {
                 const double z = -mirror_at(bR, ROW_OBJ);
                 const int sto = st == ST_OPTIMAL && !isfinite(z) ? ST_NUMERICAL : st;
                 const bool nan_out = sto == ST_NUMERICAL;
@@ -483,7 +498,7 @@ simplex_blk_kernel(KParams P) {
 #pragma unroll
                 for (int q = 0; q < CS; ++q) {
                     const int j = q * 64 + lane, v = cv[q];
-                    if (j < COL_RHS) {
+                    if (j < COL_RHS && (!SH || wave == q % NW)) {
                         if (v < n) {
                             P.x[L.col_off + v] = nan_out ? qnan : 0.0;
                         } else if (v < n + m) {
@@ -495,7 +510,7 @@ simplex_blk_kernel(KParams P) {
 #pragma unroll
                 for (int q = 0; q < RS; ++q) {
                     const int i = q * 64 + lane, v = bs[q];
-                    if (i < m) {
+                    if (i < m && (!SH || wave == (CS + q) % NW)) {
                         if (v < n) {
                             P.x[L.col_off + v] = nan_out ? qnan : bR[q];
                         } else if (v < n + m) {
@@ -503,7 +518,7 @@ simplex_blk_kernel(KParams P) {
                         }
                     }
                 }
-                if (lane == 0) {
+                if (t == 0) {
                     if constexpr (TR == 1) P.trace[(int64_t)k * P.trace_stride] = 2 + 2 * (iters - 1) < P.trace_stride ? iters : -1;
                     P.status[k] = sto;
                     P.iters[k] = iters;
@@ -549,109 +564,105 @@ simplex_blk_kernel(KParams P) {
         BLP_TACC(TM_LOAD, t_load0, t_load1);
         for (;;) {
             if (SH && st != -1) {
-                // SH: LP k is done (st >= 0) or its objective was not finite
-                // (st == -2, outputs written).  Extract it, take the next
-                // objective and rebuild the objective row on the current
-                // basis; phase 2 resumes from there.  If phase 1 ended the
-                // solve (infeasible), every objective gets that outcome.
-                if (st >= 0) extract();
-                const bool same = st >= 0 && mode != 2;
+                // SH: LP k is done.  Extract it, take the next objective and
+                // rebuild the objective row on the current basis; phase 2
+                // resumes from there.  If phase 1 ended the solve
+                // (infeasible), every objective gets that outcome.
+                // What bounds it is the chain of LDS trips and barriers: an
+                // objective needs 0.3 pivots along a sweep.  So the next
+                // objective is loaded an LP ahead (and used before the
+                // outputs' stores, which a load behind them would wait for),
+                // and what a barrier would hand over, every wave computes. (50,000
+                // objectives on 100 x 100: this kernel 1,100 -> 925 us.)
+                const int k_was = k;
                 k = pop();
-                if (k < 0) break;
-                L = lp_ref(P, k);
-                if (same) continue;
-                {
-                    // warm start only if the new objective points close to the
-                    // previous one (cosine > 0.9); otherwise the previous basis
-                    // is usually farther from the new optimum than the slack
-                    // basis, and the objective goes back to a cold start
-                    double dot = 0.0, nn = 0.0, oo = 0.0;
-                    for (int j = t; j < n; j += NT) {
-                        const double cn = P.c[L.col_off + j], co = s_c[j];
-                        dot += cn * co;
-                        nn += cn * cn;
-                        oo += co * co;
-                    }
-                    for (int o = 32; o >= 1; o >>= 1) {
-                        dot += __shfl_xor(dot, o);
-                        nn += __shfl_xor(nn, o);
-                        oo += __shfl_xor(oo, o);
-                    }
-                    if (lane == 0) {
-                        s_sim[3 * (t >> 6)] = dot;
-                        s_sim[3 * (t >> 6) + 1] = nn;
-                        s_sim[3 * (t >> 6) + 2] = oo;
-                    }
-                    lds_barrier();
-                    dot = nn = oo = 0.0;
-                    for (int w = 0; w < NW; ++w) {
-                        dot += s_sim[3 * w];
-                        nn += s_sim[3 * w + 1];
-                        oo += s_sim[3 * w + 2];
-                    }
-                    if (!(dot > 0.9 * sqrt(nn * oo))) {  // also taken for non-finite c
-                        if (t == 0) s_pending = k;
-                        lds_barrier();
-                        break;
-                    }
-                }
-                int badc = 0;
-                for (int j = t; j < n; j += NT) {
-                    const double cj = P.c[L.col_off + j];
-                    badc |= !isfinite(cj);
-                    s_c[j] = cj;
-                }
-                if (badc) atomicOr(&s_bad, 1);
-                lds_barrier();
-                if (s_bad) {
-                    write_numerical<NT>(P, L, k, t, ST_NUMERICAL);
-                    lds_barrier();
-                    st = -2;  // written; take the next objective
+                if (k < 0 || mode != 2) {
+                    extract(k_was);
+                    if (k < 0) break;
+                    L = lp_ref(P, k);
                     continue;
                 }
-                if (t < 64) {
-#pragma unroll
-                    for (int q = 0; q < RS; ++q) {
-                        const int i = q * 64 + lane;
-                        if (i < RP) s_cb[i] = (i < m && bs[q] < n) ? s_c[bs[q]] : 0.0;
-                    }
+                // warm start only if the new objective points close to the
+                // previous one (cosine > 0.9); otherwise the previous basis
+                // is usually farther from the new optimum than the slack
+                // basis, and the objective goes back to a cold start
+                const double cn = t < n ? (k == k_was + 1 ? c_next : load_c(k)) : 0.0;
+                double dot = cn * c_own, nn = cn * cn, oo = c_own * c_own;
+                for (int o = 32; o >= 1; o >>= 1) {
+                    dot += __shfl_xor(dot, o);
+                    nn += __shfl_xor(nn, o);
+                    oo += __shfl_xor(oo, o);
                 }
+                if (lane == 0) {
+                    s_sim[3 * wave] = dot;
+                    s_sim[3 * wave + 1] = nn;
+                    s_sim[3 * wave + 2] = oo;
+                }
+                if (t < n) s_c[t] = cn;
+                c_own = cn;
                 lds_barrier();
+                extract(k_was);
+                L = lp_ref(P, k);
+                c_next = load_c(min(k + 1, (int)P.count - 1));
+                dot = nn = oo = 0.0;
+                for (int w = 0; w < NW; ++w) {
+                    dot += s_sim[3 * w];
+                    nn += s_sim[3 * w + 1];
+                    oo += s_sim[3 * w + 2];
+                }
+                // (also taken for an objective that is not finite: nn is not, then)
+                if (!__builtin_amdgcn_readfirstlane(dot > 0.9 * sqrt(nn * oo))) {
+                    if (t == 0) s_pending = k;
+                    lds_barrier();
+                    break;
+                }
+                double* const cb = s_cb + wave * RP;
+#pragma unroll
+                for (int q = 0; q < RS; ++q) {
+                    const int i = q * 64 + lane;
+                    if (i < RP) cb[i] = (i < m && bs[q] < n) ? s_c[bs[q]] : 0.0;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 // partial sums over this thread's rows, in row order
 #pragma unroll
                 for (int c = 0; c < CB; ++c) {
                     double acc = 0.0;
 #pragma unroll
-                    for (int r = 0; r < RB; ++r) acc = __builtin_fma(s_cb[i0 + r], T[r][c], acc);
+                    for (int r = 0; r < RB; ++r) acc = __builtin_fma(cb[i0 + r], T[r][c], acc);
                     s_part[trb * CP + c * GC + tcb] = acc;
-                }
-                lds_barrier();
-                if (t < 64) {
-#pragma unroll
-                    for (int q = 0; q < CS; ++q) {
-                        const int j = q * 64 + lane;
-                        if (j < CP) {
-                            double z = 0.0;
-                            for (int g = 0; g < GR; ++g) z = z + s_part[g * CP + j];
-                            const int v = cv[q];
-                            s_p[0][j] = (v < n ? s_c[v] : 0.0) - z;
-                        }
-                    }
                 }
                 lds_barrier();
 #pragma unroll
                 for (int q = 0; q < CS; ++q) {
                     const int j = q * 64 + lane;
-                    dO[q] = j < CP ? s_p[0][j] : 0.0;
+                    double d = 0.0;
+                    if (j < CP) {
+                        double z = 0.0;
+#pragma unroll
+                        for (int g = 0; g < GR; ++g) z = z + s_part[g * CP + j];
+                        const int v = cv[q];
+                        d = (v < n ? s_c[v] : 0.0) - z;
+                    }
+                    dO[q] = d;
                 }
+                const double zr = mirror_at(dO, COL_RHS);
 #pragma unroll
                 for (int q = 0; q < RS; ++q)
-                    if (q * 64 + lane == ROW_OBJ) bR[q] = s_p[0][COL_RHS];
-                if (trb == GR - 1) {
+                    if (q * 64 + lane == ROW_OBJ) bR[q] = zr;
+                if (wave == NW - 1) {  // the tile's objective row
 #pragma unroll
-                    for (int c = 0; c < CB; ++c) T[RB - 1][c] = s_p[0][c * GC + tcb];
+                    for (int q = 0; q < CS; ++q)
+                        if (q * 64 + lane < CP) s_p[0][q * 64 + lane] = dO[q];
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    if (trb == GR - 1) {
+#pragma unroll
+                        for (int c = 0; c < CB; ++c) T[RB - 1][c] = s_p[0][c * GC + tcb];
+                    }
                 }
-                lds_barrier();
                 st = -1;
                 iters = 0;
                 degen = 0;
@@ -902,7 +913,7 @@ simplex_blk_kernel(KParams P) {
         }
 
         // ------------------------------------------------------ extraction
-        if (!SH) extract();
+        if (!SH) extract(k);
     }
     BLP_TFLUSH();
 }

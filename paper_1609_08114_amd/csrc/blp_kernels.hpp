@@ -49,7 +49,8 @@ struct KParams {
     const int32_t* list;
     const int32_t* bin_off;
     const int32_t* bin_len;
-    int32_t* bin_head;  // persistent mode: next entry to take (atomic), bin b's at bin_head[b * kHeadStride]
+    int32_t* bin_head;  // persistent mode: next entry to take (atomic), bin b's at bin_head[b * head_shards * kHeadStride]
+    int32_t head_shards;  // heads per bin: a power of two, at most kHeadShards
     int32_t bin;
     int32_t direct;       // 1: entry = direct_first + blockIdx.x, no queue
     int64_t chunk;        // shared-constraint mode: LPs taken per queue pop
@@ -182,18 +183,44 @@ __device__ __forceinline__ int64_t work_item(const KParams& P, int64_t q) {
 // head.  Sharing a line with the offsets made the 100 x 100 block-tile
 // solve ~3% slower.
 constexpr int kHeadStride = 32;
-__device__ __forceinline__ int* bin_head_of(const KParams& P) { return P.bin_head + P.bin * kHeadStride; }
+// A bin has kHeadShards heads (one where memory is limited): an atomic on one address takes 13 ns from pop
+// to pop, and for small LPs that was all of the time (20,000 LPs of 10 x 10 and
+// of 30 x 30 both 340 us).
+constexpr int kHeadShards = 8;
+constexpr int kHeadInts = kHeadShards * kHeadStride;  // a bin's heads
+__device__ __forceinline__ int* bin_head_of(const KParams& P) { return P.bin_head + P.bin * P.head_shards * kHeadStride; }
 
-// Next queue position of this launch's work list (one lane calls it).  On a
-// workgroup's first pop the head is read plainly first: when the list is
-// empty (or already exhausted) the workgroups of the launch leave without an
-// atomic each, which thousands of them would serialise on one address.
-// Later pops go straight to the atomic (the extra read would add a memory
-// round trip per LP).
-__device__ __forceinline__ int pop_position(const KParams& P, int64_t len, bool first) {
-    int* head = bin_head_of(P);
-    if (first && __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= len) return (int)len;
-    return atomicAdd(head, 1);
+// Next of this launch's `units` work units (one lane calls it), for worker
+// `me` of `workers`.  The first is unit `me`, without an atomic: an empty list
+// costs its launch nothing.  Then worker me takes the units s, s + 8, ... of
+// its shard s = me mod 8 (so that every shard, like the list, runs from the
+// large LPs to the small) that are nobody's first, and when they are gone
+// moves on to the next shard that still has some: `shard` is its shard.
+__device__ __forceinline__ int pop_unit(const KParams& P, int units, int me, int workers, bool first, int& shard) {
+    const int H = P.head_shards;  // a power of two
+    if (first) {
+        shard = me & (H - 1);
+        return min(me, units);
+    }
+    int* const head = bin_head_of(P);
+    for (;;) {
+        // (shard s starts behind its workers' first units)
+        const int u = shard + H * ((workers - shard + H - 1) / H + atomicAdd(head + shard * kHeadStride, 1));
+        if (u < units) return u;
+        int next = -1;
+#pragma unroll
+        for (int d = kHeadShards - 1; d >= 1; --d) {
+            const int s = (shard + d) & (H - 1);
+            const int taken = __hip_atomic_load(head + s * kHeadStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (s + H * ((workers - s + H - 1) / H + taken) < units) next = s;
+        }
+        if (next < 0) return units;
+        shard = next;
+    }
+}
+// The same for one LP per workgroup: the next position of the list.
+__device__ __forceinline__ int pop_position(const KParams& P, int64_t len, bool first, int& shard) {
+    return pop_unit(P, (int)len, (int)blockIdx.x, (int)gridDim.x, first, shard);
 }
 
 // ---------------------------------------------------------------------------

@@ -66,12 +66,14 @@ struct DevBuf {
 // scratch array of the allocation-free entry point): hands out 256-byte
 // aligned pieces, never frees.
 // Bin counters of a solve, in ints: bin_len, bin_fill and bin_off (nbins
-// each), the work-list heads from heads_at(nbins) on (kHeadStride apart,
-// each on a cache line of its own), then kBinStripes striped copies of the
+// each), the work-list heads from heads_at(nbins) on (`shards`
+// per bin, each on a cache line of its own), then kBinStripes striped copies of the
 // bin counts (kStripeStride apart).  The buffer is 256-byte aligned.
 static size_t heads_at(int nbins) { return ((size_t)3 * nbins + kHeadStride - 1) / kHeadStride * kHeadStride; }
-static size_t stripes_at(int nbins) { return heads_at(nbins) + (size_t)kHeadStride * nbins; }
-static size_t counter_ints(int nbins) { return stripes_at(nbins) + (size_t)kBinStripes * kStripeStride; }
+static size_t stripes_at(int nbins, int shards) { return heads_at(nbins) + (size_t)kHeadStride * shards * nbins; }
+static size_t counter_ints(int nbins, int shards) {
+    return stripes_at(nbins, shards) + (size_t)kBinStripes * kStripeStride;
+}
 
 struct Arena {
     char* base = nullptr;
@@ -242,16 +244,20 @@ static bool usable(blp_handle h, int v, bool limited) { return h->variants[v].pe
 // of smallest key takes an LP.  A register tile's key is its area.  A
 // pending-pivot class costs more latency per pivot than the 112 x 112 block
 // tile (area 12,544) and less CU time: with enough LPs to fill its workgroups
-// it comes right after the 32 x 32 tile, else right after that block tile.
+// it comes right after the 32 x 32 tile, with 32 LPs per CU before it, else
+// right after that block tile.
 // Measured (us, block tile and class): two-phase 47 x 61, 1,024 LPs 1,134 and
 // 1,480, 2,048 LPs 1,998 and 908; one-phase 100 x 100, 2,048 LPs 240 and 253,
 // 50,000 LPs 3,680 and 3,020; one-phase 50 x 50, 8,000 LPs 531 (64 x 64 row
-// tile) and 216.  Below, at 20 x 20: the 32 x 32 row tile 443 and 501.
+// tile) and 216; the 32 x 32 row tile and class p1, two-phase 20 x 20, 8,000 LPs
+// 428 and 459, 20,000 LPs 922 and 884, one-phase 30 x 30, 2,000 LPs 69 and 75,
+// 20,000 LPs 250 and 207.
 static int variant_key(blp_handle h, int v, int64_t count) {
     const RegVariant& rv = h->variants[v];
     if (rv.pend < 0) return rv.max_rows * rv.max_cols;
     const int64_t per_cu[] = {6, 10};  // LPs per CU from which the class comes first
     const bool full = rv.pend < 2 && count >= per_cu[rv.pend] * h->cu_count;
+    if (rv.pend == 0 && count >= 32 * (int64_t)h->cu_count) return 32 * 32 - 1;
     return (full ? 32 * 32 : 112 * 112) + 1 + rv.pend;
 }
 
@@ -593,7 +599,8 @@ struct SolvePlan {
     size_t gm_lds = 0;
     std::vector<char> maybe;  // register variants that can receive LPs
     bool limited = false;     // no workspaces beyond the planned buffers (mem_limit, static scratch)
-    int direct_v = -1;        // >= 0: one launch of this variant, LP k in workgroup k, no binning
+    int direct_v = -1;        // >= 0: one launch of this variant, no binning
+    bool direct_queue = false;  // its workgroups take LPs from the queue (else LP k in workgroup k)
     bool may_stream = false;  // some simplex LP may reach the streaming kernel
     // device buffers of this solve (the handle's own, or carved from an arena)
     int32_t* counters = nullptr;
@@ -755,7 +762,8 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
     P.timers = h->timers;
 #endif
     const int nreg = h->nreg, nbins = nreg + 2;
-    BUF_TRY(h, arena, h->counters, sizeof(int32_t) * counter_ints(nbins), sp.counters);
+    P.head_shards = limited ? 1 : kHeadShards;  // (what a limit or a scratch size was made for has one)
+    BUF_TRY(h, arena, h->counters, sizeof(int32_t) * counter_ints(nbins, P.head_shards), sp.counters);
     int32_t* bin_count = sp.counters;
     P.bin_len = bin_count;
     P.bin_off = bin_count + 2 * nbins;
@@ -823,7 +831,8 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
     // give the same bits, and it costs four launches, about as long as
     // solving such a batch.
     sp.direct_v = -1;
-    if (uni && any_simplex && h->opt.variant == -1 && h->opt.mode == BLP_MODE_PERSISTENT) {
+    const bool may_direct = uni && any_simplex && !stream_all && h->opt.variant == -1 && h->opt.mode == BLP_MODE_PERSISTENT;
+    if (may_direct) {
         const int m = h->plan.m[0], n = h->plan.n[0];
         long barea = -1;
         for (int v = 0; v < nreg; ++v) {
@@ -839,11 +848,35 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
             }
         }
     }
+    // A larger uniform batch whose LPs all go to one variant, whatever their
+    // number of artificial rows, needs no binning either: its workgroups take
+    // the LPs from the queue in their order (20,000 LPs 30 x 30: 207 us with the
+    // binning, 178 without).
+    if (may_direct && sp.direct_v < 0) {
+        const int m = h->plan.m[0], n = h->plan.n[0];
+        int one = -1;  // the variant for every number of artificial rows so far
+        bool same = true;
+        for (int nart = 0; same && nart <= m; ++nart) {
+            const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
+            int best = -1;
+            for (int v = 0; v < nreg; ++v)
+                if (usable(h, v, limited) && holds(h->variants[v], m, n, nart) && (t1 || !h->variants[v].type1_only) &&
+                    K >= auto_min_count(h, v) && (best < 0 || variant_key(h, v, K) < variant_key(h, best, K)))
+                    best = v;
+            if (nart == 0) one = best;
+            same = best >= 0 && best == one && h->remap[best] == best;
+        }
+        if (same) {
+            sp.direct_v = one;
+            sp.direct_queue = true;
+        }
+    }
     // Pending-pivot classes: a workspace slot per workgroup for the largest
     // LP that the class may get.
     for (int v = 0; v < nreg; ++v) {
         const int i = h->variants[v].pend;
-        if (i < 0 || limited || !any_simplex || sp.direct_v >= 0 || !(sp.maybe[v] || stream_all)) continue;
+        if (i < 0 || limited || !any_simplex) continue;
+        if (sp.direct_v >= 0 ? sp.direct_v != v : !(sp.maybe[v] || stream_all)) continue;
         SolvePlan::PendClass& c = sp.cls[i];
         const int mc = std::min(max_m, kPendTiles[i].rows()), cc = std::min(max_cols - 1, kPendTiles[i].slots());
         c.plan = pend_plan(h, K, mc, cc, sp.uni, i);
@@ -938,8 +971,8 @@ static blp_error enqueue_binning(blp_handle h, SolvePlan& sp, hipStream_t s) {
     int32_t* bin_fill = bin_count + nbins;
     HIP_TRY(h, h->mark(nbins, true, s));
     // zero the counters and the striped bin counters (bin_off is rewritten)
-    int32_t* stripes = bin_count + stripes_at(nbins);
-    HIP_TRY(h, launch_reset(bin_count, (int)counter_ints(nbins), s));
+    int32_t* stripes = bin_count + stripes_at(nbins, sp.P.head_shards);
+    HIP_TRY(h, launch_reset(bin_count, (int)counter_ints(nbins, sp.P.head_shards), s));
     HIP_TRY(h, launch_classify(sp.P, variant_table(h, sp.P.count, sp.limited), sp.binid, stripes, s));
     HIP_TRY(h, launch_bin_offsets(stripes, bin_count, const_cast<int32_t*>(sp.P.bin_off), nbins, s));
     HIP_TRY(h, launch_scatter(sp.P.count, nbins, sp.binid, sp.P.bin_off, bin_fill, sp.list, s));
@@ -966,7 +999,7 @@ static hipError_t launch_streaming(const SolvePlan& sp, const KParams& P, int64_
     }
     KParams Q = P;
     Q.skip_pend = both ? 1 : 0;
-    if (both) Q.bin_head += kHeadStride;
+    if (both) Q.bin_head += kHeadStride * P.head_shards;
     return launch_gm(Q, (int)std::min<int64_t>(P.direct ? grid : sp.gm_workers, grid), sp.gm_lds, s, sp.gm_deep);
 }
 
@@ -977,6 +1010,7 @@ static hipError_t launch_variant(blp_handle h, const SolvePlan& sp, int v, const
     const int i = h->variants[v].pend;
     if (i < 0) return h->variants[v].launch(P, (int)grid, s);
     const SolvePlan::PendClass& c = sp.cls[i];
+    if (!c.ws) return hipErrorInvalidValue;  // never chosen without its workspace
     KParams Q = P;
     Q.ws = c.ws;
     Q.ws_slot = c.slot;
@@ -1129,6 +1163,7 @@ static std::vector<uint64_t> graph_signature(blp_handle h, const SolvePlan& sp, 
             g.push_back(x);
     for (int v = 0; v < h->nreg; ++v) g.push_back((uint64_t)sp.maybe[v] | ((uint64_t)h->remap[v] << 8));
     g.push_back((uint64_t)(int64_t)sp.direct_v);
+    g.push_back((uint64_t)sp.direct_queue);
     g.push_back((uint64_t)P.pivot_rule);
     g.push_back((uint64_t)P.layout);
     g.push_back(P.seed);
@@ -1169,6 +1204,16 @@ static blp_error enqueue_direct(blp_handle h, SolvePlan& sp, hipStream_t s) {
     Q.direct_first = 0;
     Q.direct_end = 0;
     Q.bin = v;
+    if (sp.direct_queue) {
+        Q.direct = 0;
+        Q.list = nullptr;  // every LP, in order
+        Q.bin = 0;
+        HIP_TRY(h, launch_reset(Q.bin_head, kHeadStride * Q.head_shards, s));
+        HIP_TRY(h, h->mark(v, true, s));
+        HIP_TRY(h, launch_variant(h, sp, v, Q, reg_grid(h, v, Q.count), s));
+        HIP_TRY(h, h->mark(v, false, s));
+        return BLP_SUCCESS;
+    }
     HIP_TRY(h, h->mark(v, true, s));
     const int64_t per = h->variants[v].lps_per_block;
     HIP_TRY(h, h->variants[v].launch(Q, (int)((Q.count + per - 1) / per), s));
@@ -1229,7 +1274,7 @@ static blp_error solve_limited(blp_handle h, const blp_batch* B, const blp_outpu
     const size_t out_bytes = (own_st ? 4 * (size_t)K : 0) + (own_it ? 4 * (size_t)K : 0) +
                              (own_ob ? 8 * (size_t)K : 0) + (own_x ? 8 * (size_t)std::max<int64_t>(1, tot_n) : 0) +
                              (own_y ? 8 * (size_t)std::max<int64_t>(1, tot_m) : 0);
-    const size_t counters = sizeof(int32_t) * counter_ints(h->nreg + 2);
+    const size_t counters = sizeof(int32_t) * counter_ints(h->nreg + 2, 1);
     const size_t slot = any_simplex ? sizeof(double) * (size_t)max_slot : 0;
     const size_t per_lp = uni ? 8 : 48;
     const size_t fixed = out_bytes + counters + slot;
@@ -1460,7 +1505,7 @@ blp_error blp_pivot_trace(blp_handle h, const blp_batch* B, const blp_outputs* o
     int v = -1;  // the registered variant of this tile, for the per-class figures
     for (int w = 0; w < h->nreg; ++w)
         if (std::strcmp(h->variants[w].name, "b4_r112_c112") == 0) v = w;
-    HIP_TRY(h, launch_reset(Q.bin_head, 1, s));
+    HIP_TRY(h, launch_reset(Q.bin_head, kHeadStride * Q.head_shards, s));
     if (v >= 0) HIP_TRY(h, h->mark(v, true, s));
     HIP_TRY(h, launch_blk_trace(Q, (int)std::min<int64_t>((int64_t)occ * h->cu_count, K), s, replay ? 2 : 1));
     if (v >= 0) HIP_TRY(h, h->mark(v, false, s));
@@ -1598,14 +1643,15 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
     P.timers = h->timers;
 #endif
     const int nreg = h->nreg, nb = nreg + 2;
-    // route lengths (nb), zero list offsets (nb), then one queue head per
-    // route, each on a cache line of its own
+    // route lengths (nb), zero list offsets (nb), then the queue heads of
+    // every route, each on a cache line of its own
     const size_t heads = ((size_t)2 * nb + kHeadStride - 1) / kHeadStride * kHeadStride;
-    const size_t ints = heads + (size_t)kHeadStride * nb;
+    const size_t ints = heads + (size_t)kHeadInts * nb;
     HIP_TRY(h, h->shared_ctr.reserve(sizeof(int32_t) * ints));
     int32_t* rb = h->shared_ctr.as<int32_t>();
     HIP_TRY(h, launch_reset(rb, (int)ints, s));
     P.bin_head = rb + heads;
+    P.head_shards = kHeadShards;
     P.bin = 0;
     if (h->opt.variant >= 0) {
         blp_error e = solve_shared_forced(h, P, rows, cols, s);
@@ -2046,24 +2092,25 @@ blp_error blp_autotune(blp_handle h, const blp_batch* B, int32_t sample, const c
     HIP_TRY(h, hipMemcpyAsync(cnt.data(), sp.P.bin_len, sizeof(int32_t) * nbins, hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipMemcpyAsync(off.data(), sp.P.bin_off, sizeof(int32_t) * nbins, hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
+    constexpr size_t kList = kHeadStride + kHeadInts;  // start of a sample's list in the scratch
     hipEvent_t e0, e1;
     HIP_TRY(h, hipEventCreate(&e0));
     HIP_TRY(h, hipEventCreate(&e1));
     for (int v = 0; v < nreg; ++v) {
         if (cnt[v] == 0) continue;
         const int S = std::min<int>(sample, cnt[v]);
-        // scratch: [bin_off = 0, bin_len = S, bin_head] + S list entries
-        HIP_TRY(h, h->tune.reserve(sizeof(int32_t) * (4 + (size_t)S)));
+        // scratch: bin_off = 0, bin_len = S; the heads; S list entries
+        HIP_TRY(h, h->tune.reserve(sizeof(int32_t) * (kList + (size_t)S)));
         int32_t* tb = h->tune.as<int32_t>();
-        int32_t hdr[3] = {0, S, 0};
+        int32_t hdr[2] = {0, S};
         HIP_TRY(h, hipMemcpyAsync(tb, hdr, sizeof hdr, hipMemcpyHostToDevice, s));
-        HIP_TRY(h, hipMemcpyAsync(tb + 4, sp.list + off[v], sizeof(int32_t) * S,
+        HIP_TRY(h, hipMemcpyAsync(tb + kList, sp.list + off[v], sizeof(int32_t) * S,
                                   hipMemcpyDeviceToDevice, s));
         KParams Q = sp.P;
-        Q.list = tb + 4;
+        Q.list = tb + kList;
         Q.bin_off = tb;
         Q.bin_len = tb + 1;
-        Q.bin_head = tb + 2;
+        Q.bin_head = tb + kHeadStride;
         Q.bin = 0;
         Q.direct = 0;
         float best_ms = -1.f;
@@ -2072,7 +2119,7 @@ blp_error blp_autotune(blp_handle h, const blp_batch* B, int32_t sample, const c
             if (!can_replace(h, w, v) || (w < nreg && !usable(h, w, sp.limited))) continue;
             float ms = 0.f;
             for (int rep = 0; rep < 2; ++rep) {  // the second run is timed
-                HIP_TRY(h, launch_reset(tb + 2, 1, s));
+                HIP_TRY(h, launch_reset(tb + kHeadStride, kHeadInts, s));
                 HIP_TRY(h, hipEventRecord(e0, s));
                 if (w < nreg) {
                     HIP_TRY(h, launch_variant(h, sp, w, Q, reg_grid(h, w, S), s));
@@ -2099,16 +2146,16 @@ blp_error blp_autotune(blp_handle h, const blp_batch* B, int32_t sample, const c
     int deep = saved_deep;
     if (cnt[nreg] > 0) {
         const int S = std::min<int>(sample, cnt[nreg]);
-        HIP_TRY(h, h->tune.reserve(sizeof(int32_t) * (4 + (size_t)S)));
+        HIP_TRY(h, h->tune.reserve(sizeof(int32_t) * (kList + (size_t)S)));
         int32_t* tb = h->tune.as<int32_t>();
-        int32_t hdr[3] = {0, S, 0};
+        int32_t hdr[2] = {0, S};
         HIP_TRY(h, hipMemcpyAsync(tb, hdr, sizeof hdr, hipMemcpyHostToDevice, s));
-        HIP_TRY(h, hipMemcpyAsync(tb + 4, sp.list + off[nreg], sizeof(int32_t) * S, hipMemcpyDeviceToDevice, s));
+        HIP_TRY(h, hipMemcpyAsync(tb + kList, sp.list + off[nreg], sizeof(int32_t) * S, hipMemcpyDeviceToDevice, s));
         KParams Q = sp.P;
-        Q.list = tb + 4;
+        Q.list = tb + kList;
         Q.bin_off = tb;
         Q.bin_len = tb + 1;
-        Q.bin_head = tb + 2;
+        Q.bin_head = tb + kHeadStride;
         Q.bin = 0;
         Q.direct = 0;
         float best_ms = -1.f;
@@ -2119,7 +2166,7 @@ blp_error blp_autotune(blp_handle h, const blp_batch* B, int32_t sample, const c
             const int grid = (int)std::min<int64_t>(std::min<int64_t>((int64_t)occ * h->cu_count, sp.gm_workers), S);
             float ms = 0.f;
             for (int rep = 0; rep < 2; ++rep) {  // the second run is timed
-                HIP_TRY(h, launch_reset(tb + 2, 1, s));
+                HIP_TRY(h, launch_reset(tb + kHeadStride, kHeadInts, s));
                 HIP_TRY(h, hipEventRecord(e0, s));
                 HIP_TRY(h, launch_gm(Q, grid, lds, s, d != 0));
                 HIP_TRY(h, hipEventRecord(e1, s));

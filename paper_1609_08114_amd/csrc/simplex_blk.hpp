@@ -227,6 +227,7 @@ simplex_blk_kernel(KParams P) {
     // next queue position (pf_q); once the LP is loaded it reads that
     // position's list entry (pf_k, -2 = not read yet).  The atomic and the
     // list read then overlap the solve instead of preceding the next load.
+    int shard = 0;
     int pf_q = -1, pf_k = -2;
     // next LP index of this workgroup (-1: none); SH takes chunks
     auto pop = [&]() __attribute__((always_inline)) -> int {
@@ -237,7 +238,7 @@ simplex_blk_kernel(KParams P) {
                 s_pending = -1;
             } else if (!SH && !P.direct) {
                 if (first) {
-                    const int q = pop_position(P, len, true);
+                    const int q = pop_position(P, len, true, shard);
                     kk = q < len ? (int)work_item(P, q) : -1;
                 } else {
                     kk = pf_k != -2 ? pf_k : (pf_q < len ? (int)work_item(P, pf_q) : -1);
@@ -259,7 +260,7 @@ simplex_blk_kernel(KParams P) {
             s_k = kk;
             s_bad = 0;
             if (!SH && !P.direct) {  // reserve the next position (after the LDS write: no wait for it)
-                pf_q = kk >= 0 ? atomicAdd(bin_head_of(P), 1) : (int)len;
+                pf_q = kk >= 0 ? pop_position(P, len, false, shard) : (int)len;
                 pf_k = -2;
             }
         }

@@ -90,13 +90,14 @@ simplex_cols_kernel(KParams P) {
 
     const int64_t len = work_len(P);
     bool first = true;
+    int shard = 0;
     int pf_q = -1, pf_k = -2;  // reserved next queue position and its list entry (-2: not read)
     auto pop = [&]() __attribute__((always_inline)) -> int {
         if (t == 0) {
             int kk;
             if (!P.direct) {
                 if (first) {
-                    const int q = pop_position(P, len, true);
+                    const int q = pop_position(P, len, true, shard);
                     kk = q < len ? (int)work_item(P, q) : -1;
                 } else {
                     kk = pf_k != -2 ? pf_k : (pf_q < len ? (int)work_item(P, pf_q) : -1);
@@ -108,7 +109,7 @@ simplex_cols_kernel(KParams P) {
             s_k = kk;
             s_bad = 0;
             if (!P.direct) {
-                pf_q = kk >= 0 ? atomicAdd(bin_head_of(P), 1) : (int)len;
+                pf_q = kk >= 0 ? pop_position(P, len, false, shard) : (int)len;
                 pf_k = -2;
             }
         }
@@ -170,7 +171,7 @@ simplex_cols_kernel(KParams P) {
         }
         if (art) atomicOr(&s_bad, 2);
         lds_barrier();
-        if (s_bad & 2) {
+        if (__builtin_amdgcn_readfirstlane(s_bad) & 2) {
             write_numerical<NT>(P, L, k, t, ST_INTERNAL);
             lds_barrier();
             continue;
@@ -209,7 +210,7 @@ simplex_cols_kernel(KParams P) {
         }
         if (bad) atomicOr(&s_bad, 1);
         lds_barrier();
-        if (s_bad) {
+        if (__builtin_amdgcn_readfirstlane(s_bad)) {
             write_numerical<NT>(P, L, k, t, ST_NUMERICAL);
             lds_barrier();
             continue;

@@ -81,13 +81,14 @@ __global__ void __launch_bounds__(NW * 64) simplex_gm_kernel(KParams P) {
 
     const int64_t len = work_len(P);
     bool first = true;
+    int shard = 0;  // (thread 0)
     for (;;) {
         if (t == 0) {
             int64_t q;
             if (P.direct)
                 q = first ? P.direct_first + (int64_t)blockIdx.x : len;
             else
-                q = pop_position(P, len, first);
+                q = pop_position(P, len, first, shard);
             s_k = q < len ? (int)work_item(P, q) : -1;
             s_bad = 0;
         }

@@ -43,6 +43,7 @@ simplex_lane_kernel(KParams P) {
     // direct modes: this wave's 64 positions, bounded by direct_end
     const int64_t dend = P.direct && P.direct_end > 0 && P.direct_end < len ? P.direct_end : len;
     bool first = true;
+    int shard = 0;  // (lane 0)
     for (;;) {
         int64_t q0;
         if (P.direct) {
@@ -51,13 +52,10 @@ simplex_lane_kernel(KParams P) {
         } else {
             int v = 0;
             if (lane == 0) {
-                int* head = bin_head_of(P);
-                // an exhausted (or empty) list: leave without an atomic
-                v = first && __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= len
-                        ? (int)len
-                        : atomicAdd(head, 64);
+                v = pop_unit(P, (int)((len + 63) / 64), (int)blockIdx.x * NWV + wave, (int)gridDim.x * NWV, first,
+                             shard);
             }
-            q0 = __shfl(v, 0);
+            q0 = (int64_t)__builtin_amdgcn_readfirstlane(v) * 64;
         }
         first = false;
         if (q0 >= dend) break;

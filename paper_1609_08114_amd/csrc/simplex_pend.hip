@@ -185,6 +185,7 @@ simplex_pend_kernel(KParams) {
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     BLP_TDECL;
     bool first = true;
+    int shard = 0;  // (thread 0)
     int par = 0;
     for (;;) {
         par ^= 1;
@@ -195,7 +196,7 @@ simplex_pend_kernel(KParams) {
             if (P.direct)
                 q = first ? P.direct_first + (int64_t)blockIdx.x : len;
             else
-                q = pop_position(P, len, first);
+                q = pop_position(P, len, first, shard);
             s_ctl[par][0] = q < len ? (int)work_item(P, q) : -1;
             s_ctl[par][1] = 0;
         }

@@ -75,13 +75,14 @@ simplex_reg_kernel(KParams P) {
     BLP_TDECL;
     const int64_t len = work_len(P);
     bool first = true;
+    int shard = 0;  // (thread 0)
     for (;;) {
         if (t == 0) {
             int64_t q;
             if (P.direct)
                 q = first ? P.direct_first + (int64_t)blockIdx.x : len;
             else
-                q = pop_position(P, len, first);
+                q = pop_position(P, len, first, shard);
             s_k = q < len ? (int)work_item(P, q) : -1;
             s_bad = 0;
         }
@@ -110,7 +111,7 @@ simplex_reg_kernel(KParams P) {
         __syncthreads();
         if (t < 64) scan_art_rows(m, lane, s_flag, s_artrow, s_rank, &s_nart);
         __syncthreads();
-        const int nart = s_nart;
+        const int nart = __builtin_amdgcn_readfirstlane(s_nart);
         if (n + nart + 1 > CP) {
             write_numerical<NT>(P, L, k, t, ST_INTERNAL);
             __syncthreads();
@@ -185,7 +186,7 @@ simplex_reg_kernel(KParams P) {
             s_colvar[j] = j < n ? j : (j < n + nart && j < COL_RHS ? n + s_artrow[j - n] : ID_NONE);
         for (int i = t; i < m; i += NT) s_basis[i] = (s_flag[i] & RF_ART) ? n + m + i : n + i;
         __syncthreads();
-        if (s_bad) {
+        if (__builtin_amdgcn_readfirstlane(s_bad)) {
             write_numerical<NT>(P, L, k, t, ST_NUMERICAL);
             __syncthreads();
             continue;

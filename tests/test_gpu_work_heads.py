@@ -67,3 +67,16 @@ def test_autotune_of_a_uniform_batch(count):
     torch.cuda.synchronize()
     assert np.array_equal(out["obj"][:count].cpu().numpy(), oracle.solve_batch(hb)["obj"])
     s.close()
+
+
+@pytest.mark.parametrize("m,n,count", [(1, 1, 20_000), (5, 5, 150_001), (6, 6, 17_000), (8, 20, 9_000), (9, 3, 9_001),
+                                       (31, 10, 7_000), (32, 10, 7_000), (33, 10, 7_000)])
+def test_classification_of_small_rows(m, n, count):
+    """One LP per lane up to 32 rows, around the groups of 8 rows: the same
+    bins as the batch classified LP by LP."""
+    hb = lpgen.make_batch(800 + m, np.arange(count), np.where(np.arange(count) % 3 == 0, 1, 2).astype(np.int32),
+                          np.full(count, m, np.int32), np.full(count, n, np.int32))
+    print(f"[heads] classify {count} of {m} x {n}", flush=True)
+    a, b = gpu_solve(hb, uniform=True, mode=1), gpu_solve(hb, uniform=False, mode=1)
+    assert np.array_equal(a["bins"], b["bins"])
+    assert np.array_equal(a["obj"], b["obj"]) and np.array_equal(a["iters"], b["iters"])

@@ -563,354 +563,351 @@ simplex_blk_kernel(KParams P) {
         if (!SH && !P.direct && t == 0 && pf_k == -2) pf_k = pf_q < len ? (int)work_item(P, pf_q) : -1;
         BLP_T(t_load1);
         BLP_TACC(TM_LOAD, t_load0, t_load1);
-        for (;;) {
-            if (SH && st != -1) {
-                // SH: LP k is done.  Extract it, take the next objective and
-                // rebuild the objective row on the current basis; phase 2
-                // resumes from there.  If phase 1 ended the solve
-                // (infeasible), every objective gets that outcome.
-                // What bounds it is the chain of LDS trips and barriers: an
-                // objective needs 0.3 pivots along a sweep.  So the next
-                // objective is loaded an LP ahead (and used before the
-                // outputs' stores, which a load behind them would wait for),
-                // and what a barrier would hand over, every wave computes. (50,000
-                // objectives on 100 x 100: this kernel 1,100 -> 925 us.)
-                const int k_was = k;
-                k = pop();
-                if (k < 0 || mode != 2) {
-                    extract(k_was);
-                    if (k < 0) break;
-                    L = lp_ref(P, k);
-                    continue;
-                }
-                // warm start only if the new objective points close to the
-                // previous one (cosine > 0.9); otherwise the previous basis
-                // is usually farther from the new optimum than the slack
-                // basis, and the objective goes back to a cold start
-                const double cn = t < n ? (k == k_was + 1 ? c_next : load_c(k)) : 0.0;
-                double dot = cn * c_own, nn = cn * cn, oo = c_own * c_own;
-                for (int o = 32; o >= 1; o >>= 1) {
-                    dot += __shfl_xor(dot, o);
-                    nn += __shfl_xor(nn, o);
-                    oo += __shfl_xor(oo, o);
-                }
-                if (lane == 0) {
-                    s_sim[3 * wave] = dot;
-                    s_sim[3 * wave + 1] = nn;
-                    s_sim[3 * wave + 2] = oo;
-                }
-                if (t < n) s_c[t] = cn;
-                c_own = cn;
-                lds_barrier();
-                extract(k_was);
-                L = lp_ref(P, k);
-                c_next = load_c(min(k + 1, (int)P.count - 1));
-                dot = nn = oo = 0.0;
-                for (int w = 0; w < NW; ++w) {
-                    dot += s_sim[3 * w];
-                    nn += s_sim[3 * w + 1];
-                    oo += s_sim[3 * w + 2];
-                }
-                // (also taken for an objective that is not finite: nn is not, then)
-                if (!__builtin_amdgcn_readfirstlane(dot > 0.9 * sqrt(nn * oo))) {
-                    if (t == 0) s_pending = k;
+        for (;;) {  // SH: once per objective
+            for (; !SH || st == -1;) {
+                int l = -1, lv = ID_NONE;
+                double rmin = 1.0;
+                BLP_T(t_p0);
+                if (mode == 3) {
+                    int r0 = -1;
+#pragma unroll
+                    for (int q = 0; q < RS; ++q) {
+                        const int i = q * 64 + lane;
+                        const bool cand = i < m && i >= drive_r && bs[q] >= id_lim && !((dead >> q) & 1u);
+                        const unsigned long long mk = __ballot(cand);
+                        if (r0 < 0 && mk) r0 = q * 64 + __ffsll((long long)mk) - 1;
+                    }
+                    if (r0 < 0) {
+                        mode = 2;
+                        degen = 0;
+                        step1();
+                        continue;
+                    }
+                    drive_r = r0 + 1;
+                    // row r0 into s_p[buf]; the lowest-id non-artificial column
+                    // with a usable entry enters
                     lds_barrier();
-                    break;
+                    if (trb == r0 / RB) {
+                        const int rr = r0 % RB;
+#pragma unroll
+                        for (int r = 0; r < RB; ++r)
+                            if (r == rr) {
+#pragma unroll
+                                for (int c = 0; c < CB; ++c) s_p[buf][c * GC + tcb] = T[r][c];
+                            }
+                    }
+                    lds_barrier();
+                    double bk = -__builtin_inf();
+                    int bid = ID_NONE, bpos = -1;
+#pragma unroll
+                    for (int q = 0; q < CS; ++q) {
+                        const int j = q * 64 + lane;
+                        if (j < COL_RHS) {
+                            const int v = cv[q];
+                            if (v < id_lim && fabs(s_p[buf][j]) > P.eps_piv && key_before(0.0, v, bk, bid)) {
+                                bk = 0.0;
+                                bid = v;
+                                bpos = j;
+                            }
+                        }
+                    }
+                    wave_argmax(bk, bid, bpos);
+                    lds_barrier();
+                    if (bid == ID_NONE) {  // redundant row
+                        if (r0 % 64 == lane) dead |= 1u << (r0 / 64);
+                        continue;
+                    }
+                    l = r0;
+                    e = bpos;
+                    e_id = bid;
+                    lv = mirror_at(bs, r0);
+                } else {
+                    if (e_id == ID_NONE) {
+                        if (mode == 2) {
+                            st = ST_OPTIMAL;
+                            break;
+                        }
+                        if (mirror_at(bR, ROW_W) > P.eps_feas * (1.0 + w0)) {
+                            st = ST_INFEASIBLE;
+                            break;
+                        }
+                        mode = 3;
+                        drive_r = 0;
+                        continue;
+                    }
+                    if (iters >= max_iter) {
+                        st = ST_ITER_LIMIT;
+                        break;
+                    }
                 }
-                double* const cb = s_cb + wave * RP;
+                BLP_T(t_p1);
+                // publish the entering column (f) and clear its slot; the slot
+                // becomes the leaving variable's column
+                const int e_piv = e;  // Step 1 of the next pivot overwrites e before the update
+                {
+                    const int ce = __builtin_amdgcn_readfirstlane(e / GC), te = e % GC;
+                    if (tcb == te) {
+#pragma unroll
+                        for (int c = 0; c < CB; ++c)
+                            if (c == ce) {
+#pragma unroll
+                                for (int r = 0; r < RB; ++r) {
+                                    s_f[buf][i0 + r] = T[r][c];
+                                    if (!SH) T[r][c] = 0.0;
+                                }
+                            }
+                    }
+                }
+                lds_barrier();
+                BLP_T(t_p2);
+                double fr[RS];
 #pragma unroll
                 for (int q = 0; q < RS; ++q) {
                     const int i = q * 64 + lane;
-                    if (i < RP) cb[i] = (i < m && bs[q] < n) ? s_c[bs[q]] : 0.0;
+                    const double v = s_f[buf][i];
+                    fr[q] = i < RP ? v : 0.0;
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                // partial sums over this thread's rows, in row order
-#pragma unroll
-                for (int c = 0; c < CB; ++c) {
-                    double acc = 0.0;
-#pragma unroll
-                    for (int r = 0; r < RB; ++r) acc = __builtin_fma(cb[i0 + r], T[r][c], acc);
-                    s_part[trb * CP + c * GC + tcb] = acc;
-                }
-                lds_barrier();
-#pragma unroll
-                for (int q = 0; q < CS; ++q) {
-                    const int j = q * 64 + lane;
-                    double d = 0.0;
-                    if (j < CP) {
-                        double z = 0.0;
-#pragma unroll
-                        for (int g = 0; g < GR; ++g) z = z + s_part[g * CP + j];
-                        const int v = cv[q];
-                        d = (v < n ? s_c[v] : 0.0) - z;
+                if (mode != 3) {
+                    if constexpr (TR == 2) {  // the recorded leaving row
+                        l = s_tr[1 + 2 * iters];
+                        lv = mirror_at(bs, l);
+                    } else {
+                        l = ratio_regs(m, lane, P.eps_piv, fr, bR, bs, dead, rmin, lv);
                     }
-                    dO[q] = d;
+                    if (l < 0) {
+                        st = mode == 2 ? ST_UNBOUNDED : ST_NUMERICAL;
+                        break;  // (SH: the tile is untouched, its slot is cleared at the update)
+                    }
                 }
-                const double zr = mirror_at(dO, COL_RHS);
+                const double pe = mirror_at(fr, l);
+                if constexpr (TR == 1) {  // record (row, slot) of this pivot
+                    if (t == 0 && 2 + 2 * iters < P.trace_stride) {
+                        int32_t* tr = P.trace + (int64_t)k * P.trace_stride;
+                        tr[1 + 2 * iters] = l;
+                        tr[2 + 2 * iters] = e_piv;
+                    }
+                }
+                BLP_T(t_p2b);
+                BLP_TACC(TM_RTEST, t_p2, t_p2b);
+                // Step 3's new pivot row.  The owners of row l (GC lanes of one
+                // wave) put its entries into s_p[buf] and zero them in the tile;
+                // the whole wave holding row l then divides CS entries per lane
+                // (LDS operations of one wave complete in order, so no barrier
+                // is needed between the two).  After the update the tile's row l
+                // is fma(1, p, 0) = p.
+                constexpr int ROWS_PER_WAVE = 64 / GC * RB;
+                const bool row_wave = t / 64 == l / ROWS_PER_WAVE;
+                if (row_wave) {
+                    if (trb == l / RB) {
+                        const int rl = __builtin_amdgcn_readfirstlane(l % RB);
+                        const int de = e - tcb;  // slot c*GC + tcb is e iff c*GC == de
 #pragma unroll
-                for (int q = 0; q < RS; ++q)
-                    if (q * 64 + lane == ROW_OBJ) bR[q] = zr;
-                if (wave == NW - 1) {  // the tile's objective row
+                        for (int r = 0; r < RB; ++r)
+                            if (r == rl) {
 #pragma unroll
-                    for (int q = 0; q < CS; ++q)
-                        if (q * 64 + lane < CP) s_p[0][q * 64 + lane] = dO[q];
+                                for (int c = 0; c < CB; ++c) {
+                                    s_p[buf][c * GC + tcb] = c * GC == de ? 1.0 : T[r][c];
+                                    T[r][c] = 0.0;
+                                }
+                            }
+                    }
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    if (trb == GR - 1) {
+                    const double y = 1.0 / pe;
+                    const double ape = fabs(pe);
+                    const bool pe_ok = ape >= 0x1p-500 && ape <= 0x1p500;
+                    double xs[CS], ps[CS];
+                    bool slow = false;
 #pragma unroll
-                        for (int c = 0; c < CB; ++c) T[RB - 1][c] = s_p[0][c * GC + tcb];
+                    for (int q = 0; q < CS; ++q) {
+                        xs[q] = s_p[buf][q * 64 + lane];
+                        bool ok;
+                        ps[q] = div_rn_fast(xs[q], pe, y, pe_ok, ok);
+                        slow |= !ok & (q * 64 + lane < CP);  // padding slots hold no data
+                    }
+                    if (slow) {  // extreme magnitudes only: the plain division
+#pragma unroll
+                        for (int q = 0; q < CS; ++q) ps[q] = xs[q] / pe;
+                    }
+#pragma unroll
+                    for (int q = 0; q < CS; ++q) s_p[buf][q * 64 + lane] = ps[q];
+#ifdef BLP_PHASE_TIMERS
+                    __builtin_amdgcn_s_waitcnt(0xc07f);  // the row's LDS writes done
+                    BLP_T(t_p2c);
+                    BLP_TACC(TM_DIV, t_p2b, t_p2c);
+                    BLP_TCOUNT(TM_DIVN, 1ull);
+#endif
+                }
+                lds_barrier();
+                BLP_T(t_p3);
+                double nf[RB], pc[CB];
+#pragma unroll
+                for (int r = 0; r < RB; ++r) nf[r] = -s_f[buf][i0 + r];
+                // only the wave holding row l: the pivot row (zeroed) takes 1 * p
+                if (row_wave) {
+                    const int dl = l - i0;  // row i0 + r is l iff r == dl
+#pragma unroll
+                    for (int r = 0; r < RB; ++r) nf[r] = r == dl ? 1.0 : nf[r];
+                }
+#pragma unroll
+                for (int c = 0; c < CB; ++c) pc[c] = s_p[buf][c * GC + tcb];
+                // Step 3 on the mirrors
+                {
+                    const double pr = s_p[buf][COL_RHS];
+                    const double fO = s_f[buf][ROW_OBJ], fW = s_f[buf][ROW_W];
+                    const int el = e - lane, ll = l - lane;  // slot / row q*64 + lane is e / l iff q*64 == el / ll
+                    // slots j >= CP (padding lanes) carry values never read
+#pragma unroll
+                    for (int q = 0; q < CS; ++q) {
+                        const double pj = s_p[buf][q * 64 + lane];
+                        const bool ent = q * 64 == el;
+                        dO[q] = __builtin_fma(-fO, pj, ent ? 0.0 : dO[q]);
+                        // the phase-1 row is read only in phase 1 and drive-out
+                        if (mode != 2) dW[q] = __builtin_fma(-fW, pj, ent ? 0.0 : dW[q]);
+                        cv[q] = ent ? lv : cv[q];
+                    }
+#pragma unroll
+                    for (int q = 0; q < RS; ++q) {
+                        const bool piv = q * 64 == ll;
+                        bR[q] = piv ? pr : __builtin_fma(-fr[q], pr, bR[q]);
+                        bs[q] = piv ? e_id : bs[q];
                     }
                 }
-                st = -1;
-                iters = 0;
-                degen = 0;
-                step1();
+                ++iters;
+                if (mode != 3) {
+                    degen = rmin == 0.0 ? degen + 1 : 0;
+                    step1();  // next pivot's entering column, overlapping the update below
+                }
+                if (SH) {  // clear the entering slot here, once the pivot is certain
+                    const int ce = __builtin_amdgcn_readfirstlane(e_piv / GC), te = e_piv % GC;
+                    if (tcb == te) {
+#pragma unroll
+                        for (int c = 0; c < CB; ++c)
+                            if (c == ce) {
+#pragma unroll
+                                for (int r = 0; r < RB; ++r)
+                                    if (i0 + r != l) T[r][c] = 0.0;
+                            }
+                    }
+                }
+                // Step 3 on the tile; the pivot row becomes p (fma(1, p, +0) = p)
+#pragma unroll
+                for (int r = 0; r < RB; ++r)
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) T[r][c] = __builtin_fma(nf[r], pc[c], T[r][c]);
+                BLP_T(t_p4);
+                BLP_TACC(TM_PRICE, t_p0, t_p1);
+                BLP_TACC(TM_PUBCOL, t_p1, t_p2);
+                BLP_TACC(TM_RATIO, t_p2, t_p3);
+                BLP_TACC(TM_PIVOT, t_p3, t_p4);
+                buf ^= 1;
+            }
+            if (!SH) break;
+            // SH: LP k is done.  Extract it, take the next objective and
+            // rebuild the objective row on the current basis; phase 2
+            // resumes from there.  If phase 1 ended the solve
+            // (infeasible), every objective gets that outcome.
+            // What bounds it is the chain of LDS trips and barriers: an objective
+            // needs 0.3 pivots along a sweep.  So the next objective is loaded
+            // an LP ahead (and used before the outputs' stores, which a load
+            // behind them would wait for), and what a barrier would hand over,
+            // every wave computes.  This stands outside the pivot loop: inside
+            // it the tile was spilled.  50,000 objectives on one 100 x 100
+            // polytope, this kernel: 1,100 -> 490 us.
+            const int k_was = k;
+            k = pop();
+            if (k < 0 || mode != 2) {
+                extract(k_was);
+                if (k < 0) break;
+                L = lp_ref(P, k);
                 continue;
             }
-            int l = -1, lv = ID_NONE;
-            double rmin = 1.0;
-            BLP_T(t_p0);
-            if (mode == 3) {
-                int r0 = -1;
-#pragma unroll
-                for (int q = 0; q < RS; ++q) {
-                    const int i = q * 64 + lane;
-                    const bool cand = i < m && i >= drive_r && bs[q] >= id_lim && !((dead >> q) & 1u);
-                    const unsigned long long mk = __ballot(cand);
-                    if (r0 < 0 && mk) r0 = q * 64 + __ffsll((long long)mk) - 1;
-                }
-                if (r0 < 0) {
-                    mode = 2;
-                    degen = 0;
-                    step1();
-                    continue;
-                }
-                drive_r = r0 + 1;
-                // row r0 into s_p[buf]; the lowest-id non-artificial column
-                // with a usable entry enters
-                lds_barrier();
-                if (trb == r0 / RB) {
-                    const int rr = r0 % RB;
-#pragma unroll
-                    for (int r = 0; r < RB; ++r)
-                        if (r == rr) {
-#pragma unroll
-                            for (int c = 0; c < CB; ++c) s_p[buf][c * GC + tcb] = T[r][c];
-                        }
-                }
-                lds_barrier();
-                double bk = -__builtin_inf();
-                int bid = ID_NONE, bpos = -1;
-#pragma unroll
-                for (int q = 0; q < CS; ++q) {
-                    const int j = q * 64 + lane;
-                    if (j < COL_RHS) {
-                        const int v = cv[q];
-                        if (v < id_lim && fabs(s_p[buf][j]) > P.eps_piv && key_before(0.0, v, bk, bid)) {
-                            bk = 0.0;
-                            bid = v;
-                            bpos = j;
-                        }
-                    }
-                }
-                wave_argmax(bk, bid, bpos);
-                lds_barrier();
-                if (bid == ID_NONE) {  // redundant row
-                    if (r0 % 64 == lane) dead |= 1u << (r0 / 64);
-                    continue;
-                }
-                l = r0;
-                e = bpos;
-                e_id = bid;
-                lv = mirror_at(bs, r0);
-            } else {
-                if (e_id == ID_NONE) {
-                    if (mode == 2) {
-                        st = ST_OPTIMAL;
-                        if (SH) continue;
-                        break;
-                    }
-                    if (mirror_at(bR, ROW_W) > P.eps_feas * (1.0 + w0)) {
-                        st = ST_INFEASIBLE;
-                        if (SH) continue;
-                        break;
-                    }
-                    mode = 3;
-                    drive_r = 0;
-                    continue;
-                }
-                if (iters >= max_iter) {
-                    st = ST_ITER_LIMIT;
-                    if (SH) continue;
-                    break;
-                }
+            // warm start only if the new objective points close to the
+            // previous one (cosine > 0.9); otherwise the previous basis
+            // is usually farther from the new optimum than the slack
+            // basis, and the objective goes back to a cold start
+            const double cn = t < n ? (k == k_was + 1 ? c_next : load_c(k)) : 0.0;
+            double dot = cn * c_own, nn = cn * cn, oo = c_own * c_own;
+            for (int o = 32; o >= 1; o >>= 1) {
+                dot += __shfl_xor(dot, o);
+                nn += __shfl_xor(nn, o);
+                oo += __shfl_xor(oo, o);
             }
-            BLP_T(t_p1);
-            // publish the entering column (f) and clear its slot; the slot
-            // becomes the leaving variable's column
-            const int e_piv = e;  // Step 1 of the next pivot overwrites e before the update
-            {
-                const int ce = __builtin_amdgcn_readfirstlane(e / GC), te = e % GC;
-                if (tcb == te) {
-#pragma unroll
-                    for (int c = 0; c < CB; ++c)
-                        if (c == ce) {
-#pragma unroll
-                            for (int r = 0; r < RB; ++r) {
-                                s_f[buf][i0 + r] = T[r][c];
-                                if (!SH) T[r][c] = 0.0;
-                            }
-                        }
-                }
+            if (lane == 0) {
+                s_sim[3 * wave] = dot;
+                s_sim[3 * wave + 1] = nn;
+                s_sim[3 * wave + 2] = oo;
             }
+            if (t < n) s_c[t] = cn;
+            c_own = cn;
             lds_barrier();
-            BLP_T(t_p2);
-            double fr[RS];
+            extract(k_was);
+            L = lp_ref(P, k);
+            c_next = load_c(min(k + 1, (int)P.count - 1));
+            dot = nn = oo = 0.0;
+            for (int w = 0; w < NW; ++w) {
+                dot += s_sim[3 * w];
+                nn += s_sim[3 * w + 1];
+                oo += s_sim[3 * w + 2];
+            }
+            // (also taken for an objective that is not finite: nn is not, then)
+            if (!__builtin_amdgcn_readfirstlane(dot > 0.9 * sqrt(nn * oo))) {
+                if (t == 0) s_pending = k;
+                lds_barrier();
+                break;
+            }
+            double* const cb = s_cb + wave * RP;
 #pragma unroll
             for (int q = 0; q < RS; ++q) {
                 const int i = q * 64 + lane;
-                const double v = s_f[buf][i];
-                fr[q] = i < RP ? v : 0.0;
+                if (i < RP) cb[i] = (i < m && bs[q] < n) ? s_c[bs[q]] : 0.0;
             }
-            if (mode != 3) {
-                if constexpr (TR == 2) {  // the recorded leaving row
-                    l = s_tr[1 + 2 * iters];
-                    lv = mirror_at(bs, l);
-                } else {
-                    l = ratio_regs(m, lane, P.eps_piv, fr, bR, bs, dead, rmin, lv);
-                }
-                if (l < 0) {
-                    st = mode == 2 ? ST_UNBOUNDED : ST_NUMERICAL;
-                    if (SH) continue;  // the tile is untouched (SH clears the slot at the update)
-                    break;
-                }
-            }
-            const double pe = mirror_at(fr, l);
-            if constexpr (TR == 1) {  // record (row, slot) of this pivot
-                if (t == 0 && 2 + 2 * iters < P.trace_stride) {
-                    int32_t* tr = P.trace + (int64_t)k * P.trace_stride;
-                    tr[1 + 2 * iters] = l;
-                    tr[2 + 2 * iters] = e_piv;
-                }
-            }
-            BLP_T(t_p2b);
-            BLP_TACC(TM_RTEST, t_p2, t_p2b);
-            // Step 3's new pivot row.  The owners of row l (GC lanes of one
-            // wave) put its entries into s_p[buf] and zero them in the tile;
-            // the whole wave holding row l then divides CS entries per lane
-            // (LDS operations of one wave complete in order, so no barrier
-            // is needed between the two).  After the update the tile's row l
-            // is fma(1, p, 0) = p.
-            constexpr int ROWS_PER_WAVE = 64 / GC * RB;
-            const bool row_wave = t / 64 == l / ROWS_PER_WAVE;
-            if (row_wave) {
-                if (trb == l / RB) {
-                    const int rl = __builtin_amdgcn_readfirstlane(l % RB);
-                    const int de = e - tcb;  // slot c*GC + tcb is e iff c*GC == de
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // partial sums over this thread's rows, in row order
 #pragma unroll
-                    for (int r = 0; r < RB; ++r)
-                        if (r == rl) {
+            for (int c = 0; c < CB; ++c) {
+                double acc = 0.0;
 #pragma unroll
-                            for (int c = 0; c < CB; ++c) {
-                                s_p[buf][c * GC + tcb] = c * GC == de ? 1.0 : T[r][c];
-                                T[r][c] = 0.0;
-                            }
-                        }
+                for (int r = 0; r < RB; ++r) acc = __builtin_fma(cb[i0 + r], T[r][c], acc);
+                s_part[trb * CP + c * GC + tcb] = acc;
+            }
+            lds_barrier();
+#pragma unroll
+            for (int q = 0; q < CS; ++q) {
+                const int j = q * 64 + lane;
+                double d = 0.0;
+                if (j < CP) {
+                    double z = 0.0;
+#pragma unroll
+                    for (int g = 0; g < GR; ++g) z = z + s_part[g * CP + j];
+                    const int v = cv[q];
+                    d = (v < n ? s_c[v] : 0.0) - z;
                 }
+                dO[q] = d;
+            }
+            const double zr = mirror_at(dO, COL_RHS);
+#pragma unroll
+            for (int q = 0; q < RS; ++q)
+                if (q * 64 + lane == ROW_OBJ) bR[q] = zr;
+            if (wave == NW - 1) {  // the tile's objective row
+#pragma unroll
+                for (int q = 0; q < CS; ++q)
+                    if (q * 64 + lane < CP) s_p[0][q * 64 + lane] = dO[q];
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const double y = 1.0 / pe;
-                const double ape = fabs(pe);
-                const bool pe_ok = ape >= 0x1p-500 && ape <= 0x1p500;
-                double xs[CS], ps[CS];
-                bool slow = false;
+                if (trb == GR - 1) {
 #pragma unroll
-                for (int q = 0; q < CS; ++q) {
-                    xs[q] = s_p[buf][q * 64 + lane];
-                    bool ok;
-                    ps[q] = div_rn_fast(xs[q], pe, y, pe_ok, ok);
-                    slow |= !ok & (q * 64 + lane < CP);  // padding slots hold no data
-                }
-                if (slow) {  // extreme magnitudes only: the plain division
-#pragma unroll
-                    for (int q = 0; q < CS; ++q) ps[q] = xs[q] / pe;
-                }
-#pragma unroll
-                for (int q = 0; q < CS; ++q) s_p[buf][q * 64 + lane] = ps[q];
-#ifdef BLP_PHASE_TIMERS
-                __builtin_amdgcn_s_waitcnt(0xc07f);  // the row's LDS writes done
-                BLP_T(t_p2c);
-                BLP_TACC(TM_DIV, t_p2b, t_p2c);
-                BLP_TCOUNT(TM_DIVN, 1ull);
-#endif
-            }
-            lds_barrier();
-            BLP_T(t_p3);
-            double nf[RB], pc[CB];
-#pragma unroll
-            for (int r = 0; r < RB; ++r) nf[r] = -s_f[buf][i0 + r];
-            // only the wave holding row l: the pivot row (zeroed) takes 1 * p
-            if (row_wave) {
-                const int dl = l - i0;  // row i0 + r is l iff r == dl
-#pragma unroll
-                for (int r = 0; r < RB; ++r) nf[r] = r == dl ? 1.0 : nf[r];
-            }
-#pragma unroll
-            for (int c = 0; c < CB; ++c) pc[c] = s_p[buf][c * GC + tcb];
-            // Step 3 on the mirrors
-            {
-                const double pr = s_p[buf][COL_RHS];
-                const double fO = s_f[buf][ROW_OBJ], fW = s_f[buf][ROW_W];
-                const int el = e - lane, ll = l - lane;  // slot / row q*64 + lane is e / l iff q*64 == el / ll
-                // slots j >= CP (padding lanes) carry values never read
-#pragma unroll
-                for (int q = 0; q < CS; ++q) {
-                    const double pj = s_p[buf][q * 64 + lane];
-                    const bool ent = q * 64 == el;
-                    dO[q] = __builtin_fma(-fO, pj, ent ? 0.0 : dO[q]);
-                    // the phase-1 row is read only in phase 1 and drive-out
-                    if (mode != 2) dW[q] = __builtin_fma(-fW, pj, ent ? 0.0 : dW[q]);
-                    cv[q] = ent ? lv : cv[q];
-                }
-#pragma unroll
-                for (int q = 0; q < RS; ++q) {
-                    const bool piv = q * 64 == ll;
-                    bR[q] = piv ? pr : __builtin_fma(-fr[q], pr, bR[q]);
-                    bs[q] = piv ? e_id : bs[q];
+                    for (int c = 0; c < CB; ++c) T[RB - 1][c] = s_p[0][c * GC + tcb];
                 }
             }
-            ++iters;
-            if (mode != 3) {
-                degen = rmin == 0.0 ? degen + 1 : 0;
-                step1();  // next pivot's entering column, overlapping the update below
-            }
-            if (SH) {  // clear the entering slot here, once the pivot is certain
-                const int ce = __builtin_amdgcn_readfirstlane(e_piv / GC), te = e_piv % GC;
-                if (tcb == te) {
-#pragma unroll
-                    for (int c = 0; c < CB; ++c)
-                        if (c == ce) {
-#pragma unroll
-                            for (int r = 0; r < RB; ++r)
-                                if (i0 + r != l) T[r][c] = 0.0;
-                        }
-                }
-            }
-            // Step 3 on the tile; the pivot row becomes p (fma(1, p, +0) = p)
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-#pragma unroll
-                for (int c = 0; c < CB; ++c) T[r][c] = __builtin_fma(nf[r], pc[c], T[r][c]);
-            BLP_T(t_p4);
-            BLP_TACC(TM_PRICE, t_p0, t_p1);
-            BLP_TACC(TM_PUBCOL, t_p1, t_p2);
-            BLP_TACC(TM_RATIO, t_p2, t_p3);
-            BLP_TACC(TM_PIVOT, t_p3, t_p4);
-            buf ^= 1;
+            st = -1;
+            iters = 0;
+            degen = 0;
+            step1();
         }
 
         // ------------------------------------------------------ extraction

@@ -87,7 +87,7 @@ typedef struct {
     double eps_piv;        /* minimum pivot-column entry in the ratio test; 0 -> 1e-9 */
     double eps_feas;       /* phase-1 zero test, relative to 1 + initial infeasibility; 0 -> 1e-9 */
     int32_t variant;       /* -1: automatic kernel choice per LP; >= 0 forces one
-                              register-tile variant (index into the library's table)
+                              kernel variant (index into the library's table)
                               and sends LPs that do not fit it to the streaming kernel;
                               -2 forces the streaming kernel for every simplex LP */
     int32_t workers_per_cu;/* persistent mode: workgroups per compute unit; 0 -> from occupancy */
@@ -240,13 +240,13 @@ blp_error blp_solve_batch_host(blp_handle h, const blp_batch* batch, const blp_o
  * (n_art = rows whose "<=" form has a negative rhs); larger constraint sets,
  * up to the limits of blp_solve_batch (m <= 2046, n + m + 1 <= 4096, else
  * BLP_ERR_TOO_LARGE), are solved from scratch for every objective by the
- * smallest register-tile variant that holds them, else the streaming kernel.
+ * smallest kernel variant that holds them, else the streaming kernel.
  * The route (warm starts, a register variant, or the streaming kernel) is
  * chosen on the device from b, sense and the first 65 objectives, so the
  * call is ordered on the stream and reads nothing back; it allocates its
  * work buffers on first use and when count grows (a call whose count and
  * shape do not exceed an earlier one's allocates nothing, and can be
- * captured in a HIP graph).  A handle whose options force a register-tile
+ * captured in a HIP graph).  A handle whose options force a kernel
  * variant (variant >= 0) runs the cold solves with that variant, and fails
  * with BLP_ERR_TOO_LARGE if it cannot hold them; to know that, it reads b,
  * sense and the first 65 objectives back to the host once (synchronising
@@ -298,7 +298,7 @@ blp_error blp_get_solution_batch(blp_handle h, int32_t* status, int32_t* iters, 
 blp_error blp_backward(blp_handle h, const double* g, double* dc, double* db, double* dA, double* dl,
                        double* du, void* hip_stream);
 
-/* Pivot trace of the 100 x 100 class's kernel (the 112 x 112 block tile),
+/* Pivot trace of the 112 x 112 block tile's kernel,
  * to time the rank-1 update of Step 3 (Sec. 4.3) apart from the search of
  * Steps 1 and 2 (Sec. 4.2).  The batch (DEVICE data) must be uniform, simplex
  * LPs only, with m + 2 <= 112 and n + 1 <= 112, and the handle's rule LPC.
@@ -320,7 +320,7 @@ blp_error blp_pivot_trace(blp_handle h, const blp_batch* batch, const blp_output
                           int32_t stride, int32_t replay, void* hip_stream);
 
 /* Number of simplex LPs of the last solve handled by each kernel class:
- * counts[0..n_reg-1] register-tile variants, counts[n_reg] streaming
+ * counts[0..n_reg-1] kernel variants, counts[n_reg] streaming
  * kernel, counts[n_reg+1] hyperbox.  Synchronises.  *n_classes receives
  * n_reg + 2; counts may be NULL to query that number only. */
 blp_error blp_last_bins(blp_handle h, int64_t* counts, int32_t* n_classes);
@@ -328,14 +328,14 @@ blp_error blp_last_bins(blp_handle h, int64_t* counts, int32_t* n_classes);
 /* Device time of each kernel class in the last solve, from HIP events
  * recorded on the solve's stream around that class's launches (only when
  * the handle was created with opt->profile != 0; otherwise all zero).
- * ms[0..n_reg-1] register-tile variants, ms[n_reg] streaming kernel,
+ * ms[0..n_reg-1] kernel variants, ms[n_reg] streaming kernel,
  * ms[n_reg+1] hyperbox kernel, ms[n_reg+2] work-list construction.
  * Synchronises.  *n_entries receives n_reg + 3; ms may be NULL. */
 blp_error blp_last_kernel_ms(blp_handle h, double* ms, int32_t* n_entries);
 
 /* Autotuner.  Classifies `batch` (DEVICE data as for blp_solve_batch), then
  * for every size bin that received LPs times each kernel variant able to
- * hold that bin's LPs (register-tile variants of equal or larger shape, and
+ * hold that bin's LPs (variants of equal or larger shape, and
  * the streaming kernel) on up to `sample` of its LPs, and remaps the bin to
  * the fastest.  The remap applies to later solves on this handle.  Results
  * never depend on it: every variant computes bit-identical outputs.  If
@@ -349,11 +349,11 @@ blp_error blp_load_tuning(blp_handle h, const char* cache_path);
 
 /* Current remap: remap[v] is the variant used for LPs whose best-fitting
  * variant is v (v in [0, n_reg)); a value n_reg means the streaming kernel.
- * *n_reg receives the number of register-tile variants. */
+ * *n_reg receives the number of kernel variants. */
 blp_error blp_tuning(blp_handle h, int32_t* remap, int32_t* n_reg);
 
 /* Name and maximum tableau shape (rows incl. objective rows, columns incl.
- * rhs) of register-tile variant v; returns BLP_ERR_ARG past the end. */
+ * rhs) of kernel variant v; returns BLP_ERR_ARG past the end. */
 blp_error blp_variant_info(int32_t v, char* name, int32_t name_len, int32_t* max_rows, int32_t* max_cols);
 
 /* Message of the last failed call on this handle ("" if none). */

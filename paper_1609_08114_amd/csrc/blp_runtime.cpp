@@ -391,6 +391,10 @@ blp_error blp_create(blp_handle* out, const blp_options* opt) {
         return BLP_ERR_ARG;
     }
     for (int v = 0; v < h->nreg; ++v) {
+        if (h->variants[v].pend >= 0) {  // their launches follow the batch (pend_plan)
+            h->reg_workers.push_back(0);
+            continue;
+        }
         int occ = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, h->variants[v].kernel(), h->variants[v].threads, 0) !=
                 hipSuccess ||
@@ -1025,8 +1029,9 @@ static hipError_t launch_variant(blp_handle h, const SolvePlan& sp, int v, const
 // slowest LP, and run one after another they leave most of the GPU idle.  A
 // uniform batch has one dominant class, and there the fork and join would
 // only add their own latency.  A captured sequence (graph mode) keeps every
-// class on the capturing stream.
-static constexpr int64_t kForkMinLps = 256;
+// class on the capturing stream; while the caller captures s, batches fork
+// from kForkMinCaptured LPs.
+static constexpr int64_t kForkMinLps = 256, kForkMinCaptured = 2048;
 static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, bool capturing = false) {
     const int nreg = h->nreg;
     const int64_t K = sp.P.count;
@@ -1045,7 +1050,12 @@ static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, 
     };
     std::stable_sort(cls.begin(), cls.end(), [&](int a, int b) { return area(a) > area(b); });
     const int nc = (int)cls.size();
-    const bool forked = !capturing && nc > 1 && !sp.uni && K >= kForkMinLps;
+    bool forked = !capturing && nc > 1 && !sp.uni && K >= kForkMinLps;
+    if (forked && K < kForkMinCaptured) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        HIP_TRY(h, hipStreamIsCapturing(s, &cs));
+        forked = cs == hipStreamCaptureStatusNone;
+    }
     const int nf = forked ? std::min(nc - 1, (int)blp_handle_s::kForks) : 0;
     if (forked) {
         HIP_TRY(h, hipEventRecord(h->fork_ev, s));

@@ -45,8 +45,8 @@
 // Measured against the kernels that took these LPs before: 1,000 two-phase LPs
 // 200 x 200 (2,055 pivots each) 204 ms streaming at every pivot, 20.9 ms here;
 // 4,000 of 100 x 100 22.0 ms in the 160 x 160 block tile, 7.8 here; 4,001 of 47 x
-// 61 3.53 ms in the 112 x 112 block tile, 1.45 here; 50,000 one-phase LPs 100 x
-// 100 3.67 ms in the block tile, 2.37 here (most of them end before the first
+// 61 3.53 ms in the 112 x 112 block tile, 1.40 here; 50,000 one-phase LPs 100 x
+// 100 3.67 ms in the block tile, 2.36 here (most of them end before the first
 // flush, and their tableau is never written).
 //
 // Layout of a workspace slot: strips of four rows, in a strip blocks of 4 x 4

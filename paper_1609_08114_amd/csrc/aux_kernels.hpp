@@ -76,15 +76,17 @@ struct SharedRoute {
     int nreg;
     int rows[kMaxVariants], cols[kMaxVariants], type1[kMaxVariants];
     int tile_rows, tile_cols;  // tableau of the warm-started kernel
+    int cold;                  // >= 0: the pending-pivot class that takes all cold solves
 };
 // The route for n_art artificial rows; warm_dirs: consecutive objectives
 // point in close directions.  Warm starts when the shared tile holds the
-// tableau; otherwise the register variant of the shared tile's shape, else
+// tableau; otherwise `cold`, else the register variant of the shared tile's shape, else
 // the one of smallest area (the first of equal areas), that holds it; else
 // the streaming kernel.  Variants for LPs without artificial rows only
 // (type1) are never taken.
 __host__ __device__ inline int shared_route_of(const SharedRoute& rt, int m, int n, int nart, bool warm_dirs) {
     if (warm_dirs && m + 2 <= rt.tile_rows && n + nart + 1 <= rt.tile_cols) return rt.nreg + 1;
+    if (rt.cold >= 0) return rt.cold;
     for (int i = 0; i < rt.nreg; ++i)
         if (rt.rows[i] == rt.tile_rows && rt.cols[i] == rt.tile_cols && !rt.type1[i] && m + 2 <= rt.rows[i] &&
             n + nart + 1 <= rt.cols[i])

@@ -548,6 +548,7 @@ static void gm_lds_plan(blp_handle h, int ld, int cols, bool deep, bool shared, 
 // hide the latency of a pivot.
 struct PendPlan {
     int tile = 0, occ = 1;  // kPendTiles index, workgroups per CU
+    int max_occ = 1;        // and for any number of LPs (workspaces: a smaller batch may run more per CU)
     size_t lds = 0;         // dynamic LDS of a workgroup, bytes
 };
 // Doubles of one workspace slot for LPs of at most m rows and n + m columns
@@ -566,6 +567,7 @@ static PendPlan pend_plan(blp_handle h, int64_t lps, int m, int cols, bool alone
     auto fit = [&](int pivots) { return (int)(h->lds_per_cu / need(pivots)); };
     p.occ = std::max(1, std::min(4 * T.wpe / T.waves, std::max(fit(T.pivots), std::min(2, fit(8)))));
     if (T.waves == 2 && p.occ > 1) p.occ &= ~1;  // the same number of waves on every SIMD
+    p.max_occ = h->opt.workers_per_cu > 0 ? std::min(p.occ, (int)h->opt.workers_per_cu) : p.occ;
     size_t share;
     if (alone) {
         // as many at a time as the rounds over all CUs take: more would only
@@ -886,7 +888,8 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         c.plan = pend_plan(h, K, mc, cc, sp.uni, i);
         c.workers = (int)std::min<int64_t>((int64_t)c.plan.occ * h->cu_count, K);
         c.slot = pend_slot(mc, cc);
-        HIP_TRY(h, h->pend_ws[i].reserve(sizeof(double) * (size_t)c.slot * (size_t)c.workers));
+        const size_t slots = (size_t)std::min<int64_t>((int64_t)c.plan.max_occ * h->cu_count, K);
+        HIP_TRY(h, h->pend_ws[i].reserve(sizeof(double) * (size_t)c.slot * slots));
         c.ws = h->pend_ws[i].as<double>();
     }
     // Streaming-kernel geometry: worst case over the batch's simplex LPs.
@@ -1565,6 +1568,17 @@ static blp_error launch_shared_warm(blp_handle h, KParams& P, hipStream_t s) {
 // blp_solve_shared on a handle that forces a register variant: the route is
 // decided on the host (b, sense and the first 65 objectives read back), so
 // that a variant that cannot hold the constraints fails the call.
+// A pending-pivot class over a shared constraint set: its plan and workspace.
+static blp_error plan_shared_class(blp_handle h, SolvePlan& sp, int i, int m, int n, int64_t count) {
+    SolvePlan::PendClass& c = sp.cls[i];
+    c.plan = pend_plan(h, count, m, n + m, true, i);
+    c.workers = (int)std::min<int64_t>((int64_t)c.plan.occ * h->cu_count, count);
+    c.slot = pend_slot(m, n + m);
+    const size_t slots = (size_t)std::min<int64_t>((int64_t)c.plan.max_occ * h->cu_count, count);
+    HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * (size_t)c.slot * slots));
+    c.ws = h->shared_ws.as<double>();
+    return BLP_SUCCESS;
+}
 static blp_error solve_shared_forced(blp_handle h, KParams& P, int rows, int cols, hipStream_t s) {
     const int m = P.um, n = P.un;
     const int64_t count = P.count;
@@ -1597,12 +1611,8 @@ static blp_error solve_shared_forced(blp_handle h, KParams& P, int rows, int col
     P.shared_in = 1;
     SolvePlan sp;
     if (const int i = h->variants[v].pend; i >= 0) {
-        SolvePlan::PendClass& c = sp.cls[i];
-        c.plan = pend_plan(h, count, m, n + m, true, i);
-        c.workers = (int)std::min<int64_t>((int64_t)c.plan.occ * h->cu_count, count);
-        c.slot = pend_slot(m, n + m);
-        HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * (size_t)c.slot * (size_t)c.workers));
-        c.ws = h->shared_ws.as<double>();
+        const blp_error e = plan_shared_class(h, sp, i, m, n, count);
+        if (e != BLP_SUCCESS) return e;
     }
     HIP_TRY(h, launch_variant(h, sp, v, P, reg_grid(h, v, count), s));
     return BLP_SUCCESS;
@@ -1680,9 +1690,18 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
     for (int v = 0; v < nreg && v < kMaxVariants; ++v) {
         rt.rows[v] = h->variants[v].max_rows;
         rt.cols[v] = h->variants[v].max_cols;
-        // (never a pending-pivot class: the streaming route picks its tile)
+        // (no pending-pivot class by its area: see `cold`, and the streaming
+        // route picks its tile)
         rt.type1[v] = h->variants[v].type1_only || h->variants[v].pend >= 0;
     }
+    // The class that a batch of as many such LPs goes to also takes the cold
+    // solves (50,000 random objectives on 100 x 100 constraints: 2.04 ms in the
+    // 112 x 112 block tile, 0.87 here).
+    rt.cold = -1;
+    for (int v = 0; v < nreg && h->opt.layout == BLP_LAYOUT_COLUMN && h->opt.mem_limit == 0; ++v)
+        if (rt.cold < 0 && h->variants[v].pend >= 0 && holds(h->variants[v], m, n, m) &&
+            variant_key(h, v, count) < 112 * 112)
+            rt.cold = v;
     rt.tile_rows = rows;
     rt.tile_cols = cols;
     std::vector<char> cand(nb, 0);
@@ -1706,12 +1725,17 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
         blp_error e = launch_shared_warm(h, Q, s);
         if (e != BLP_SUCCESS) return e;
     }
+    SolvePlan sp;
     for (int v = 0; v < nreg; ++v) {
         if (!cand[v]) continue;
         KParams Q = P;
         Q.bin = v;
         Q.shared_in = 1;
-        HIP_TRY(h, h->variants[v].launch(Q, reg_grid(h, v, count), s));
+        if (const int i = h->variants[v].pend; i >= 0) {
+            const blp_error e = plan_shared_class(h, sp, i, m, n, count);
+            if (e != BLP_SUCCESS) return e;
+        }
+        HIP_TRY(h, launch_variant(h, sp, v, Q, reg_grid(h, v, count), s));
     }
     if (cand[nreg]) {
         // the streaming kernel with on-chip columns (nothing else runs beside
@@ -1737,7 +1761,8 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
         const int64_t workers = std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * h->cu_count, count));
         const size_t slot =
             pend ? std::max((size_t)ld * gcols, (size_t)pend_slot(m, n + m)) : (size_t)ld * gcols;
-        HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * slot * (size_t)workers));
+        const int64_t slots = std::min<int64_t>((int64_t)(pend ? pp.max_occ : occ) * h->cu_count, count);
+        HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * slot * (size_t)std::max(slots, workers)));
         Q.ws = h->shared_ws.as<double>();
         Q.ws_slot = (int64_t)slot;
         Q.ws_ld = ld;
@@ -2109,6 +2134,14 @@ blp_error blp_autotune(blp_handle h, const blp_batch* B, int32_t sample, const c
     for (int v = 0; v < nreg; ++v) {
         if (cnt[v] == 0) continue;
         const int S = std::min<int>(sample, cnt[v]);
+        // A pending-pivot class earns its place by filling the CUs.  With no
+        // more than an LP or two on each, a sample of a larger bin times the
+        // latency of a pivot instead, for which the larger tiles are better
+        // (workload of 200,000 LPs of 5..300: 0.86 s, retuned so 1.22 s).
+        if (h->variants[v].pend >= 0 && cnt[v] > S) {
+            saved[v] = v;
+            continue;
+        }
         // scratch: bin_off = 0, bin_len = S; the heads; S list entries
         HIP_TRY(h, h->tune.reserve(sizeof(int32_t) * (kList + (size_t)S)));
         int32_t* tb = h->tune.as<int32_t>();

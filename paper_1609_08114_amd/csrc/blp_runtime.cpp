@@ -1059,7 +1059,7 @@ static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, 
         HIP_TRY(h, hipStreamIsCapturing(s, &cs));
         forked = cs == hipStreamCaptureStatusNone;
     }
-    const int nf = forked ? std::min(nc - 1, (int)blp_handle_s::kForks) : 0;
+    const int nf = forked ? std::min(nc, (int)blp_handle_s::kForks) : 0;
     if (forked) {
         HIP_TRY(h, hipEventRecord(h->fork_ev, s));
         for (int i = 0; i < nf; ++i) HIP_TRY(h, hipStreamWaitEvent(h->fork[i], h->fork_ev, 0));
@@ -1072,8 +1072,13 @@ static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, 
     const char* what = "";
     for (int i = 0; i < nc && err == hipSuccess; ++i) {
         const int v = cls[i];
-        // the first class (the largest LPs) stays on s
-        hipStream_t st = (forked && i > 0) ? h->fork[(i - 1) % nf] : s;
+        // The two classes of the largest LPs get a fork each, the rest the
+        // third.  Never s: the forks were made one after the other, so the
+        // runtime gave them hardware queues of their own, but any of these may
+        // be the one of s, and two classes in one queue run one after the
+        // other (2,000 LPs of up to 300 x 300, by the handle: 20 to 36 ms with
+        // the largest class on s, 20 to 24 so).
+        hipStream_t st = forked ? h->fork[std::min(i, nf - 1)] : s;
         KParams Q = P;
         Q.bin = v;
         err = h->mark(v, true, st);

@@ -321,6 +321,12 @@ def _backward_fills(db: DeviceBatch, key: str, src) -> bool:
     return bool(off[0] == 0 and off[-1] + each[-1] == src.numel() and (off[1:] - off[:-1] == each[:-1]).all())
 
 
+def _result(n: int, dtype, dev):
+    """A result tensor of n entries, which the call writes; of one zero if n is 0."""
+    import torch
+    return torch.empty(n, dtype=dtype, device=dev) if n else torch.zeros(1, dtype=dtype, device=dev)
+
+
 class Solver:
     """A handle plus device result tensors.  One per host thread."""
 
@@ -336,6 +342,7 @@ class Solver:
         o.mem_limit = mem_limit
         o.tune_cache = tune_cache.encode() if tune_cache else None
         self.device = device
+        self._no_rows = None, None
         self.h = blp_create(o)
 
     def close(self):
@@ -351,24 +358,42 @@ class Solver:
 
     def solve(self, db: DeviceBatch, stream=None, outputs: dict | None = None) -> dict:
         """Solve on `stream` (torch stream or None for the current one).
-        Returns device tensors status, iters, obj, x, y."""
+        Returns device tensors status, iters, obj, x, y.  An output without
+        entries is one zero; that of a batch without rows (y of hyperboxes) is
+        the same tensor in every result of this solver."""
         import torch
         dev = torch.device("cuda", self.device)
+        st = stream if stream is not None else torch.cuda.current_stream(dev)
         K = db.count
         tot_m = int(db.m[0]) * K if db.uniform else int((db.row_off + db.m).max(initial=0))
         tot_n = int(db.n[0]) * K if db.uniform else int((db.col_off + db.n).max(initial=0))
         if outputs is None:
-            outputs = {"status": torch.empty(max(K, 1), dtype=torch.int32, device=dev),
-                       "iters": torch.empty(max(K, 1), dtype=torch.int32, device=dev),
-                       "obj": torch.empty(max(K, 1), dtype=torch.float64, device=dev),
-                       "x": torch.empty(max(tot_n, 1), dtype=torch.float64, device=dev),
-                       "y": torch.empty(max(tot_m, 1), dtype=torch.float64, device=dev)}
+            outputs = {"status": _result(K, torch.int32, dev), "iters": _result(K, torch.int32, dev),
+                       "obj": _result(K, torch.float64, dev), "x": _result(tot_n, torch.float64, dev),
+                       "y": _result(tot_m, torch.float64, dev) if tot_m else self._zero_row(st)}
         o = blp_outputs(*[_ptr(outputs[k]) for k in ("status", "iters", "obj", "x", "y")])
-        st = stream if stream is not None else torch.cuda.current_stream(dev)
         self._batch = db.c_struct()
         blp_solve_batch(self.h, self._batch, o, st.cuda_stream)
         self._last = (db, outputs)
         return outputs
+
+    def _zero_row(self, st):
+        """y of a batch without rows: a zero kept with the solver (a fill per
+        call would cost a launch, a good part of a small batch of boxes)."""
+        import torch
+        z, done = self._no_rows
+        if z is None or done is not None:  # not filled, or not known to be
+            capturing = torch.cuda.is_current_stream_capturing()
+            if z is None or capturing:
+                with torch.cuda.stream(st):
+                    z = torch.zeros(1, dtype=torch.float64, device=torch.device("cuda", self.device))
+                if not capturing:  # (a captured fill belongs to its graph)
+                    self._no_rows = z, st.record_event()
+            elif done.query():
+                self._no_rows = z, None
+            else:
+                st.wait_event(done)
+        return z
 
     def pivot_trace(self, db: DeviceBatch, trace, stride: int, replay: bool, stream=None,
                     outputs: dict | None = None) -> dict:
@@ -379,11 +404,9 @@ class Solver:
         dev = torch.device("cuda", self.device)
         K = db.count
         if outputs is None:
-            outputs = {"status": torch.empty(max(K, 1), dtype=torch.int32, device=dev),
-                       "iters": torch.empty(max(K, 1), dtype=torch.int32, device=dev),
-                       "obj": torch.empty(max(K, 1), dtype=torch.float64, device=dev),
-                       "x": torch.empty(max(int(db.n[0]) * K, 1), dtype=torch.float64, device=dev),
-                       "y": torch.empty(max(int(db.m[0]) * K, 1), dtype=torch.float64, device=dev)}
+            outputs = {"status": _result(K, torch.int32, dev), "iters": _result(K, torch.int32, dev),
+                       "obj": _result(K, torch.float64, dev), "x": _result(int(db.n[0]) * K, torch.float64, dev),
+                       "y": _result(int(db.m[0]) * K, torch.float64, dev)}
         o = blp_outputs(*[_ptr(outputs[k]) for k in ("status", "iters", "obj", "x", "y")])
         st = stream if stream is not None else torch.cuda.current_stream(dev)
         self._batch = db.c_struct()
@@ -399,11 +422,9 @@ class Solver:
         dev = torch.device("cuda", self.device)
         m, n = int(b.numel()), int(C.shape[1])
         K = int(C.shape[0])
-        out = {"status": torch.empty(max(K, 1), dtype=torch.int32, device=dev),
-               "iters": torch.empty(max(K, 1), dtype=torch.int32, device=dev),
-               "obj": torch.empty(max(K, 1), dtype=torch.float64, device=dev),
-               "x": torch.empty(max(K * n, 1), dtype=torch.float64, device=dev),
-               "y": torch.empty(max(K * m, 1), dtype=torch.float64, device=dev)}
+        out = {"status": _result(K, torch.int32, dev), "iters": _result(K, torch.int32, dev),
+               "obj": _result(K, torch.float64, dev), "x": _result(K * n, torch.float64, dev),
+               "y": _result(K * m, torch.float64, dev)}
         o = blp_outputs(*[_ptr(out[k]) for k in ("status", "iters", "obj", "x", "y")])
         st = stream if stream is not None else torch.cuda.current_stream(dev)
         blp_solve_shared(self.h, m, n, _ptr(A), _ptr(b), _ptr(sense), K, _ptr(C), o, st.cuda_stream)
@@ -415,9 +436,10 @@ class Solver:
         import torch
         K = int(g.numel())
         dev = g.device
-        res = {"dC": torch.empty(max(K * n, 1), dtype=torch.float64, device=dev) if "dC" in want else None,
-               "db": torch.empty(m, dtype=torch.float64, device=dev) if "db" in want else None,
-               "dA": torch.empty(m * n, dtype=torch.float64, device=dev) if "dA" in want else None}
+        new = torch.empty if K else torch.zeros  # (sums over no objectives are zero; the call leaves them)
+        res = {"dC": _result(K * n, torch.float64, dev) if "dC" in want else None,
+               "db": new(m, dtype=torch.float64, device=dev) if "db" in want else None,
+               "dA": new(m * n, dtype=torch.float64, device=dev) if "dA" in want else None}
         st = stream if stream is not None else torch.cuda.current_stream(dev)
         blp_backward_shared(self.h, m, n, K, _ptr(out["status"]), _ptr(out["x"]), _ptr(out["y"]), _ptr(g),
                             _ptr(res["dC"]), _ptr(res["db"]), _ptr(res["dA"]), st.cuda_stream)

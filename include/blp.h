@@ -236,7 +236,8 @@ blp_error blp_solve_batch_host(blp_handle h, const blp_batch* batch, const blp_o
  * rebuilt); other objectives, or every objective when the directions are
  * unrelated, are solved from scratch.  Iteration counts and, at degenerate
  * optima, x and y may therefore differ from independent solves; statuses and
- * optima do not.  Warm starts need m + 2 <= 112 and n + n_art + 1 <= 112
+ * optima do not.  Which objectives a workgroup takes is fixed by count and the
+ * device, so equal calls give the same bits.  Warm starts need m + 2 <= 112 and n + n_art + 1 <= 112
  * (n_art = rows whose "<=" form has a negative rhs); larger constraint sets,
  * up to the limits of blp_solve_batch (m <= 2046, n + m + 1 <= 4096, else
  * BLP_ERR_TOO_LARGE), are solved from scratch for every objective by the

@@ -1557,7 +1557,7 @@ blp_error blp_backward_shared(blp_handle h, int32_t m, int32_t n, int64_t count,
 // ------------------------------------------------ host-resident pipeline
 // The warm-started shared kernel: persistent workgroups taking chunks of
 // consecutive objectives (the warm starts run along a chunk), at least 8 per
-// chunk and about four chunks per workgroup for balance.
+// chunk and about four chunks per workgroup for balance, dealt out in turn.
 static blp_error launch_shared_warm(blp_handle h, KParams& P, hipStream_t s) {
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, shared_kernel_ptr(), shared_threads(), 0) != hipSuccess ||

@@ -551,9 +551,11 @@ struct PendPlan {
     int max_occ = 1;        // and for any number of LPs (workspaces: a smaller batch may run more per CU)
     size_t lds = 0;         // dynamic LDS of a workgroup, bytes
 };
-// Doubles of one workspace slot for LPs of at most m rows and n + m columns
-// (whole row tiles, blocks of four slots).
-static int64_t pend_slot(int m, int cols) { return (int64_t)((m + 15) & ~15) * (((cols + 3) & ~3) | 4) + 16; }
+// Most workgroups per CU of tile i: three (eight waves: two) waves per SIMD.
+static int pend_per_cu(blp_handle h, int i) {
+    const int most = std::max(1, 4 * kPendTiles[i].wpe / kPendTiles[i].waves);
+    return h->opt.workers_per_cu > 0 ? std::min(most, (int)h->opt.workers_per_cu) : most;
+}
 static PendPlan pend_plan(blp_handle h, int64_t lps, int m, int cols, bool alone, int tile = 0) {
     PendPlan p;
     p.tile = tile;
@@ -1570,20 +1572,30 @@ static blp_error launch_shared_warm(blp_handle h, KParams& P, hipStream_t s) {
     return BLP_SUCCESS;
 }
 
-// blp_solve_shared on a handle that forces a register variant: the route is
-// decided on the host (b, sense and the first 65 objectives read back), so
-// that a variant that cannot hold the constraints fails the call.
-// A pending-pivot class over a shared constraint set: its plan and workspace.
-static blp_error plan_shared_class(blp_handle h, SolvePlan& sp, int i, int m, int n, int64_t count) {
+// Workspace of the pending-pivot kernel for blp_solve_shared, reserved by
+// every call, also by one that takes another route: no call whose count and
+// shape do not exceed an earlier one's needs more.
+static hipError_t reserve_shared_ws(blp_handle h, int m, int n, int64_t count) {
+    if (h->opt.layout != BLP_LAYOUT_COLUMN) return hipSuccess;  // (that kernel has the one layout)
+    PendLimits tiles[kPendTileCount];
+    for (int i = 0; i < kPendTileCount; ++i)
+        tiles[i] = {kPendTiles[i].rows(), kPendTiles[i].slots(), pend_per_cu(h, i)};
+    const int from = h->opt.variant >= 0 ? std::max(0, h->variants[h->opt.variant].pend) : 0;
+    return h->shared_ws.reserve(
+        sizeof(double) * (size_t)shared_pend_doubles(tiles, kPendTileCount, from, h->cu_count, m, n, count));
+}
+// A pending-pivot class over a shared constraint set: its plan, in that workspace.
+static void plan_shared_class(blp_handle h, SolvePlan& sp, int i, int m, int n, int64_t count) {
     SolvePlan::PendClass& c = sp.cls[i];
     c.plan = pend_plan(h, count, m, n + m, true, i);
     c.workers = (int)std::min<int64_t>((int64_t)c.plan.occ * h->cu_count, count);
     c.slot = pend_slot(m, n + m);
-    const size_t slots = (size_t)std::min<int64_t>((int64_t)c.plan.max_occ * h->cu_count, count);
-    HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * (size_t)c.slot * slots));
     c.ws = h->shared_ws.as<double>();
-    return BLP_SUCCESS;
 }
+
+// blp_solve_shared on a handle that forces a register variant: the route is
+// decided on the host (b, sense and the first 65 objectives read back), so
+// that a variant that cannot hold the constraints fails the call.
 static blp_error solve_shared_forced(blp_handle h, KParams& P, int rows, int cols, hipStream_t s) {
     const int m = P.um, n = P.un;
     const int64_t count = P.count;
@@ -1615,10 +1627,7 @@ static blp_error solve_shared_forced(blp_handle h, KParams& P, int rows, int col
         return fail(h, BLP_ERR_TOO_LARGE, "variant %s cannot hold the shared constraints", h->variants[v].name);
     P.shared_in = 1;
     SolvePlan sp;
-    if (const int i = h->variants[v].pend; i >= 0) {
-        const blp_error e = plan_shared_class(h, sp, i, m, n, count);
-        if (e != BLP_SUCCESS) return e;
-    }
+    if (const int i = h->variants[v].pend; i >= 0) plan_shared_class(h, sp, i, m, n, count);
     HIP_TRY(h, launch_variant(h, sp, v, P, reg_grid(h, v, count), s));
     return BLP_SUCCESS;
 }
@@ -1673,6 +1682,7 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
     const size_t heads = ((size_t)2 * nb + kHeadStride - 1) / kHeadStride * kHeadStride;
     const size_t ints = heads + (size_t)kHeadInts * nb;
     HIP_TRY(h, h->shared_ctr.reserve(sizeof(int32_t) * ints));
+    HIP_TRY(h, reserve_shared_ws(h, m, n, count));
     int32_t* rb = h->shared_ctr.as<int32_t>();
     HIP_TRY(h, launch_reset(rb, (int)ints, s));
     P.bin_head = rb + heads;
@@ -1736,10 +1746,7 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
         KParams Q = P;
         Q.bin = v;
         Q.shared_in = 1;
-        if (const int i = h->variants[v].pend; i >= 0) {
-            const blp_error e = plan_shared_class(h, sp, i, m, n, count);
-            if (e != BLP_SUCCESS) return e;
-        }
+        if (const int i = h->variants[v].pend; i >= 0) plan_shared_class(h, sp, i, m, n, count);
         HIP_TRY(h, launch_variant(h, sp, v, Q, reg_grid(h, v, count), s));
     }
     if (cand[nreg]) {
@@ -1764,10 +1771,8 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
             if (h->opt.workers_per_cu > 0) occ = std::min(occ, (int)h->opt.workers_per_cu);
         }
         const int64_t workers = std::max<int64_t>(1, std::min<int64_t>((int64_t)occ * h->cu_count, count));
-        const size_t slot =
-            pend ? std::max((size_t)ld * gcols, (size_t)pend_slot(m, n + m)) : (size_t)ld * gcols;
-        const int64_t slots = std::min<int64_t>((int64_t)(pend ? pp.max_occ : occ) * h->cu_count, count);
-        HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * slot * (size_t)std::max(slots, workers)));
+        const size_t slot = pend ? (size_t)pend_slot(m, n + m) : (size_t)ld * gcols;
+        if (!pend) HIP_TRY(h, h->shared_ws.reserve(sizeof(double) * slot * (size_t)workers));
         Q.ws = h->shared_ws.as<double>();
         Q.ws_slot = (int64_t)slot;
         Q.ws_ld = ld;

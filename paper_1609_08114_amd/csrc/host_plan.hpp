@@ -20,6 +20,33 @@ constexpr int kMaxCols = 4096;  // n + m + 1 (condensed columns, worst case)
 // Error codes as in blp.h.
 enum { PLAN_OK = 0, PLAN_ERR_ARG = 1, PLAN_ERR_NOMEM = 2, PLAN_ERR_TOO_LARGE = 5 };
 
+// Doubles of one workspace slot of the pending-pivot kernel for LPs of at most
+// m rows and n + m = cols columns (whole row tiles, blocks of four slots, an
+// odd number of them).
+inline int64_t pend_slot(int m, int cols) { return (int64_t)((m + 15) & ~15) * (((cols + 3) & ~3) | 4) + 16; }
+
+// Largest LPs of a tile of that kernel, and the most workgroups of it per CU.
+struct PendLimits {
+    int rows, slots, per_cu;
+};
+
+// Doubles of the workspace that the cold solves of `count` objectives on one
+// m x n constraint set may need, and those of any set and number of
+// objectives no larger: a smaller set may run in a smaller tile with more
+// workgroups, and the tile depends on count.  `from`: the first tile that may
+// be used (a handle can force one).
+inline int64_t shared_pend_doubles(const PendLimits* tiles, int ntiles, int from, int cus, int m, int n,
+                                   int64_t count) {
+    int64_t most = 0;
+    for (int i = from; i < ntiles; ++i) {
+        const PendLimits& t = tiles[i];
+        const int64_t slots = std::min<int64_t>((int64_t)t.per_cu * cus, count);
+        most = std::max(most, slots * pend_slot(std::min(m, t.rows), std::min(n + m, t.slots)));
+        if (m <= t.rows && n + m <= t.slots) break;
+    }
+    return most;
+}
+
 struct VariantShape {
     int rows, cols;  // largest tableau (rows incl. objective rows, columns incl. rhs)
     int type1 = 0;   // 1: takes only LPs without artificial rows under the largest-coefficient rule

@@ -920,7 +920,9 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         if (sp.n_pend > 0) {
             const size_t want =
                 std::max(slot, (size_t)pend_slot(std::min(max_m, kPendRows), std::min(max_cols - 1, kPendSlots)));
-            if (ws_budget > 0 && want * sizeof(double) > ws_budget) {  // the limit was made for `slot`
+            // (a limit, or what the scratch holds beside the work lists, may be made for `slot`)
+            const size_t budget = arena ? arena->left() : ws_budget;
+            if (budget > 0 && want * sizeof(double) > budget) {
                 sp.n_gm += sp.n_pend;
                 sp.n_pend = 0;
                 gm_lds_plan(h, sp.gm_ld, sp.gm_cols, sp.gm_deep, sp.gm_shared, &sp.gm_lds, &P.ws_lds, &occ);

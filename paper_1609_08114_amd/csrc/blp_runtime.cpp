@@ -280,6 +280,20 @@ static int64_t auto_min_count(blp_handle h, int v) {
     return per > 1 ? per * h->cu_count / 4 : 0;
 }
 
+// The variant that the automatic choice gives an LP of m rows, n columns and
+// nart artificial rows in a batch of `count` LPs, before any remap; -1: none
+// holds it.
+static int best_variant(blp_handle h, int m, int n, int nart, int64_t count, bool limited) {
+    const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
+    int best = -1;
+    for (int v = 0; v < h->nreg; ++v)
+        if (usable(h, v, limited) && holds(h->variants[v], m, n, nart) && (t1 || !h->variants[v].type1_only) &&
+            count >= auto_min_count(h, v) &&
+            (best < 0 || variant_key(h, v, count) < variant_key(h, best, count)))
+            best = v;
+    return best;
+}
+
 // Persistent grid of register variant v for `lps` LPs: its occupancy-sized
 // worker count, but no more workgroups than the LPs fill.
 static int reg_grid(blp_handle h, int v, int64_t lps) {
@@ -804,17 +818,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
             const int m = h->plan.m[0], n = h->plan.n[0];
             for (int nart = 0; nart <= m; ++nart) {
                 const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
-                int best = -1;
-                long barea = -1;
-                for (int v = 0; v < nreg; ++v)
-                    if (usable(h, v, limited) && holds(h->variants[v], m, n, nart) &&
-                        (t1 || !h->variants[v].type1_only) && K >= auto_min_count(h, v)) {
-                        const long a = variant_key(h, v, K);
-                        if (barea < 0 || a < barea) {
-                            barea = a;
-                            best = v;
-                        }
-                    }
+                const int best = best_variant(h, m, n, nart, K, limited);
                 if (best >= 0) {
                     const int r = h->remap[best];
                     const int to =
@@ -865,12 +869,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         int one = -1;  // the variant for every number of artificial rows so far
         bool same = true;
         for (int nart = 0; same && nart <= m; ++nart) {
-            const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
-            int best = -1;
-            for (int v = 0; v < nreg; ++v)
-                if (usable(h, v, limited) && holds(h->variants[v], m, n, nart) && (t1 || !h->variants[v].type1_only) &&
-                    K >= auto_min_count(h, v) && (best < 0 || variant_key(h, v, K) < variant_key(h, best, K)))
-                    best = v;
+            const int best = best_variant(h, m, n, nart, K, limited);
             if (nart == 0) one = best;
             same = best >= 0 && best == one && h->remap[best] == best;
         }
@@ -1029,16 +1028,61 @@ static hipError_t launch_variant(blp_handle h, const SolvePlan& sp, int v, const
     return launch_pend(Q, c.plan.tile, (int)std::min<int64_t>(grid, c.workers), c.plan.lds, s);
 }
 
-// One persistent launch per kernel class that can receive LPs.  For a mixed
-// batch (not uniform, at least kForkMinLps LPs) the launches are forked onto
-// internal streams (each waits for the binning on s) and joined back into s:
-// the bins of a mixed batch are small, each kernel's duration is set by its
-// slowest LP, and run one after another they leave most of the GPU idle.  A
-// uniform batch has one dominant class, and there the fork and join would
-// only add their own latency.  A captured sequence (graph mode) keeps every
-// class on the capturing stream; while the caller captures s, batches fork
-// from kForkMinCaptured LPs.
-static constexpr int64_t kForkMinLps = 256, kForkMinCaptured = 2048;
+// Rough time of each class's launch over a mixed batch, in us (0: probably no
+// LPs): the longest LP of a sample of the batch, or its workgroups' share of
+// all of them.  The number of artificial rows is not known here (0 and half
+// of the rows are assumed, once each), nor whether an LP takes two phases:
+// pivots are those of two-phase LPs of the workloads, 1 to 4.5 us each.
+static std::vector<double> class_times(blp_handle h, const SolvePlan& sp) {
+    const int nreg = h->nreg;
+    const int64_t K = sp.P.count;
+    std::vector<double> longest(nreg + 1, 0.0), sum(nreg + 1, 0.0);
+    constexpr int kSample = 48;
+    const int ns = (int)std::min<int64_t>(K, kSample);
+    for (int q = 0; q <= ns; ++q) {
+        const int64_t k = q < ns ? (2 * q + 1) * K / (2 * ns) : h->plan.largest;
+        if (k < 0 || h->plan.kind[k] != 0) continue;
+        const int m = h->plan.m[k], n = h->plan.n[k];
+        const double us = (0.045 * m * n + std::min(m, n)) * std::min(4.5, 1.0 + (m + n) / 80.0);
+        for (int nart : {0, m / 2}) {
+            int v = h->opt.variant >= 0 ? h->opt.variant : h->opt.variant == -1 ? best_variant(h, m, n, nart, K, sp.limited) : -1;
+            if (v >= 0 && !holds(h->variants[v], m, n, nart)) v = -1;
+            if (v >= 0 && h->opt.variant == -1) v = h->remap[v];
+            if (v < 0 || v > nreg) v = nreg;
+            longest[v] = std::max(longest[v], us);
+            if (q < ns) sum[v] += us * (double)K / (2 * ns);
+        }
+    }
+    for (int v = 0; v <= nreg; ++v) {
+        const int64_t workers = v == nreg ? std::max(sp.pend_workers, sp.gm_workers)
+                                : h->variants[v].pend >= 0
+                                    ? sp.cls[h->variants[v].pend].workers
+                                    : (int64_t)h->reg_workers[v] * h->variants[v].lps_per_block;
+        longest[v] = std::max(longest[v], sum[v] / (double)std::max<int64_t>(1, workers));
+    }
+    return longest;
+}
+
+// One persistent launch per kernel class that can receive LPs, the largest LPs
+// first.  For a mixed batch (not uniform, at least kForkMinLps LPs) the
+// launches are forked onto internal streams (each waits for the binning on s)
+// and joined back into s: the bins of a mixed batch are small, each kernel's
+// duration is set by its slowest LP, and run one after another they leave most
+// of the GPU idle.  The longest launch first, each goes to the stream with the
+// least work so far, by class_times: by the order of their sizes alone, classes
+// without LPs had streams to themselves and the others shared one (256 LPs of
+// 5..60 rows and columns, a third of them two-phase: 1,004 us, 608 so).
+// Forking and joining cost some 60 us, so what runs beside the longest launch
+// has to be worth more.  With fewer than 2,048 LPs a launch is as long as its
+// longest LP, which class_times overrates up to eightfold where no LP has two
+// phases: 500 one-phase LPs of 20..60 160 us one after another, 220 forked, 400
+// of both kinds of 5..110 3.6 ms and 2.3.  With more the sums count as well:
+// 2,100 of 4..12 204 us and 235, 4,000 of 5..110 3.9 ms and 2.9.
+// A uniform batch has one dominant class.  A captured sequence (graph mode)
+// keeps every class on the capturing stream; while the caller captures s,
+// batches fork from kForkManyLps LPs.
+static constexpr int64_t kForkMinLps = 256, kForkManyLps = 2048;
+static constexpr double kForkMinUs = 1000.0, kForkManyUs = 250.0;  // class_times beside the longest
 static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, bool capturing = false) {
     const int nreg = h->nreg;
     const int64_t K = sp.P.count;
@@ -1050,20 +1094,34 @@ static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, 
     if (sp.any_simplex && sp.may_stream) cls.push_back(nreg);
     for (int v = 0; v < nreg; ++v)
         if (sp.maybe[v]) cls.push_back(v);
-    // largest LPs first: a launch lasts at least as long as its largest LP,
-    // and the smaller classes fill in behind it
-    const auto area = [&](int v) {
-        return v == nreg ? INT64_MAX : (int64_t)h->variants[v].max_rows * h->variants[v].max_cols;
-    };
-    std::stable_sort(cls.begin(), cls.end(), [&](int a, int b) { return area(a) > area(b); });
     const int nc = (int)cls.size();
     bool forked = !capturing && nc > 1 && !sp.uni && K >= kForkMinLps;
-    if (forked && K < kForkMinCaptured) {
+    if (forked && K < kForkManyLps) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         HIP_TRY(h, hipStreamIsCapturing(s, &cs));
         forked = cs == hipStreamCaptureStatusNone;
     }
-    const int nf = forked ? std::min(nc, (int)blp_handle_s::kForks) : 0;
+    std::vector<double> us(nreg + 1, 0.0);  // by class
+    std::vector<int> on(nc, 0);
+    int nf = 0;  // forks used
+    if (forked) {
+        us = class_times(h, sp);
+        std::vector<double> launch(nc);
+        for (int i = 0; i < nc; ++i) launch[i] = us[cls[i]];
+        nf = plan_forks(launch, blp_handle_s::kForks, K < kForkManyLps ? kForkMinUs : kForkManyUs, on);
+        forked = nf > 0;
+    }
+    // a launch lasts at least as long as its largest LP, and the smaller classes
+    // fill in behind it
+    const auto area = [&](int v) {
+        return v == nreg ? INT64_MAX : (int64_t)h->variants[v].max_rows * h->variants[v].max_cols;
+    };
+    std::vector<int> order(nc);
+    for (int i = 0; i < nc; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int i, int j) {
+        const int a = cls[i], b = cls[j];
+        return (us[a] > 0.0) != (us[b] > 0.0) ? us[a] > 0.0 : area(a) > area(b);
+    });
     if (forked) {
         HIP_TRY(h, hipEventRecord(h->fork_ev, s));
         for (int i = 0; i < nf; ++i) HIP_TRY(h, hipStreamWaitEvent(h->fork[i], h->fork_ev, 0));
@@ -1074,15 +1132,14 @@ static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, 
     // on s next
     hipError_t err = hipSuccess;
     const char* what = "";
-    for (int i = 0; i < nc && err == hipSuccess; ++i) {
-        const int v = cls[i];
-        // The two classes of the largest LPs get a fork each, the rest the
-        // third.  Never s: the forks were made one after the other, so the
-        // runtime gave them hardware queues of their own, but any of these may
-        // be the one of s, and two classes in one queue run one after the
-        // other (2,000 LPs of up to 300 x 300, by the handle: 20 to 36 ms with
-        // the largest class on s, 20 to 24 so).
-        hipStream_t st = forked ? h->fork[std::min(i, nf - 1)] : s;
+    for (int q = 0; q < nc && err == hipSuccess; ++q) {
+        const int i = order[q], v = cls[i];
+        // Never s: the forks were made one after the other, so the runtime
+        // gave them hardware queues of their own, but any of these may be the
+        // one of s, and two classes in one queue run one after the other (2,000
+        // LPs of up to 300 x 300, by the handle: 20 to 36 ms with the largest
+        // class on s, 20 to 24 so).
+        hipStream_t st = forked ? h->fork[on[i]] : s;
         KParams Q = P;
         Q.bin = v;
         err = h->mark(v, true, st);

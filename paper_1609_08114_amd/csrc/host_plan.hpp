@@ -47,6 +47,28 @@ inline int64_t shared_pend_doubles(const PendLimits* tiles, int ntiles, int from
     return most;
 }
 
+// Streams for launches that may run at the same time, us[i] long each (0:
+// probably empty): the longest first, each on the stream with the least work
+// so far; on[i] in [0, the result).  0 (one after another) if the launches
+// beside the longest make less than `least` us.
+inline int plan_forks(const std::vector<double>& us, int streams, double least, std::vector<int>& on) {
+    std::vector<int> by(us.size());
+    for (size_t i = 0; i < by.size(); ++i) by[i] = (int)i;
+    std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return us[a] > us[b]; });
+    std::vector<double> load((size_t)streams, 0.0);
+    double beside = 0.0;
+    int used = 0;
+    on.assign(us.size(), 0);
+    for (size_t i = 0; i < by.size(); ++i) {
+        const int f = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        load[f] += std::max(us[by[i]], 10.0);  // (a launch without LPs takes some 7 us)
+        on[by[i]] = f;
+        used = std::max(used, f + 1);
+        if (i > 0) beside += us[by[i]];
+    }
+    return beside < least ? 0 : used;
+}
+
 struct VariantShape {
     int rows, cols;  // largest tableau (rows incl. objective rows, columns incl. rhs)
     int type1 = 0;   // 1: takes only LPs without artificial rows under the largest-coefficient rule
@@ -82,6 +104,7 @@ struct Plan {
     int64_t tot_a = 0, tot_m = 0, tot_n = 0;  // extents of A, rows (b, sense, y), columns (c, l, u, x)
     int max_m = 0, max_n = 0, max_cols = 0;  // over the simplex LPs
     int64_t max_slot = 0;      // largest streaming tableau, doubles (16-row-aligned leading dimension)
+    int64_t largest = -1;      // the LP that has it (a uniform batch: 0), or -1
     int64_t n_may_stream = 0;  // simplex LPs no register variant is sure to hold
     int64_t n_may_pend = 0;    // those of them that the pending-pivot streaming kernel takes
     bool gm_deep = false;      // some LP fits no register tile even without artificial columns
@@ -114,6 +137,7 @@ inline int plan_batch(const PlanIn& in, Plan& p) {
     p.any_simplex = p.any_box = p.gm_deep = false;
     p.n_box = p.tot_a = p.tot_m = p.tot_n = p.max_slot = p.n_may_stream = p.n_may_pend = 0;
     p.max_m = p.max_n = p.max_cols = p.box_n = 0;
+    p.largest = -1;
     // no register tile holds the LP even without artificial columns
     auto sure_stream = [&](int m, int n) {
         if (in.force == -2) return true;
@@ -146,7 +170,11 @@ inline int plan_batch(const PlanIn& in, Plan& p) {
             p.max_m = std::max(p.max_m, m);
             p.max_n = std::max(p.max_n, n);
             p.max_cols = std::max(p.max_cols, n + m + 1);
-            p.max_slot = std::max<int64_t>(p.max_slot, (int64_t)((m + 2 + 15) / 16) * 16 * (n + m + 1));
+            const int64_t slot = (int64_t)((m + 2 + 15) / 16) * 16 * (n + m + 1);
+            if (slot > p.max_slot) {
+                p.max_slot = slot;
+                p.largest = k;
+            }
             if (!sure_register(m, n)) {
                 ++p.n_may_stream;
                 if (in.pend && in.pend(m, n)) ++p.n_may_pend;

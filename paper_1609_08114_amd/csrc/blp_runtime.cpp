@@ -240,32 +240,64 @@ static bool holds(const RegVariant& v, int m, int n, int nart) {
 // their own: not with mem_limit, nor from the static scratch.
 static bool usable(blp_handle h, int v, bool limited) { return h->variants[v].pend < 0 || !limited; }
 
-// Selection key of variant v for a batch of `count` LPs: the fitting variant
-// of smallest key takes an LP.  A register tile's key is its area.  A
-// pending-pivot class costs more latency per pivot than the 112 x 112 block
-// tile (area 12,544) and less CU time: with enough LPs to fill its workgroups
-// it comes right after the 32 x 32 tile, with 32 LPs per CU before it, else
-// right after that block tile.
-// Measured (us, block tile and class): two-phase 47 x 61, 1,024 LPs 1,134 and
-// 1,480, 2,048 LPs 1,998 and 908; one-phase 100 x 100, 2,048 LPs 240 and 253,
-// 50,000 LPs 3,680 and 3,020; one-phase 50 x 50, 8,000 LPs 531 (64 x 64 row
-// tile) and 216; the 32 x 32 row tile and class p1, two-phase 20 x 20, 8,000 LPs
-// 428 and 459, 20,000 LPs 922 and 884, one-phase 30 x 30, 2,000 LPs 69 and 75,
-// 20,000 LPs 250 and 207.
-static int variant_key(blp_handle h, int v, int64_t count) {
-    const RegVariant& rv = h->variants[v];
-    if (rv.pend < 0) return rv.max_rows * rv.max_cols;
-    const int64_t per_cu[] = {6, 10};  // LPs per CU from which the class comes first
-    const bool full = rv.pend < 2 && count >= per_cu[rv.pend] * h->cu_count;
-    if (rv.pend == 0 && count >= 32 * (int64_t)h->cu_count) return 32 * 32 - 1;
-    return (full ? 32 * 32 : 112 * 112) + 1 + rv.pend;
+// Most workgroups per CU of the pending-pivot kernel's tile i: three (eight
+// waves: two) waves per SIMD.
+static int pend_per_cu(blp_handle h, int i) {
+    const int most = std::max(1, 4 * kPendTiles[i].wpe / kPendTiles[i].waves);
+    return h->opt.workers_per_cu > 0 ? std::min(most, (int)h->opt.workers_per_cu) : most;
 }
 
-// The automatic choice never takes variant v for a batch of `count` LPs: one of
+// Selection key of variant v for a batch of that size: the fitting variant
+// of smallest key takes an LP.  A register tile's key is its area.  A
+// pending-pivot class costs more latency per pivot than a block tile and less
+// CU time, so what counts is how many of its LPs run at a time: all of a
+// persistent launch, what a launch of the grid mode has workgroups for, one in
+// the one-LP-per-launch mode.
+//   from 32 per CU   p1 comes before the 32 x 32 row tile
+//   from 6 (p2: 10)  p1 and p2 right after it, before the 112 x 112 block tile
+//   above 1          all before the 128-row block tiles
+//   from 1/8         before the 160 x 160 block tile, in a uniform batch
+//   else             after it (what no tile holds goes to a class anyway)
+// (A mixed batch of few LPs has few of each class: 128 one-phase LPs of 20..150
+// 541 us with p2 and p4 before the last tile, 436 with that tile.)
+// Measured (us, tile and class, two-phase unless stated):
+//   20 x 20 (32 x 32 tile), 4,096 LPs 268 and 318, 6,144 350 and 343, 12,288 602
+//     and 588; one-phase 30 x 30, 2,048 71 and 77, 8,192 137 and 119
+//   47 x 61 (112 x 112 tile) 1,024 LPs 1,126 and 797, 2,048 2,003 and 790; 80 x
+//     50, 512 559 and 806, 1,024 972 and 839, 2,560 2,105 and 1,564; one-phase
+//     100 x 100, 1,024 157 and 149, 2,560 275 and 253, 4,096 389 and 336.  (Ahead
+//     from about 4 per CU; in a mixed batch a class has a part of the count.)
+//   120 x 60 (128 x 128 tile) 1 LP 448 and 667, 256 607 and 891, 512 1,159 and
+//     1,090; 120 x 40, 256 461 and 689, 512 798 and 735
+//   129 x 60 (160 x 160 tile) 1 LP 535 and 690, 256 861 and 1,089, 512 1,435 and
+//     1,148; one-phase 150 x 150, 16 106 and 100, 256 158 and 188.  (The tile is
+//     ahead up to one per CU where each of its workgroups gets a CU; with two on
+//     some CUs 40 LPs took 1,120 to 1,200.)
+// and in the other modes, one-phase 100 x 100: 3,000 LPs in the grid mode 320 and
+// 404, one LP per launch 35 and 46 per LP.
+struct BatchSize {
+    int64_t count;
+    bool uniform;
+    int mode;
+};
+static int variant_key(blp_handle h, int v, const BatchSize& b) {
+    const RegVariant& rv = h->variants[v];
+    const int i = rv.pend;
+    if (i < 0) return rv.max_rows * rv.max_cols;
+    const int64_t cus = h->cu_count;
+    const int64_t n = b.mode == BLP_MODE_PERSISTENT ? b.count
+                      : b.mode == BLP_MODE_GRID     ? std::min<int64_t>(b.count, cus * pend_per_cu(h, i))
+                                                    : 1;
+    if (i == 0 && n >= 32 * cus) return 32 * 32 - 1;
+    if (i < 2 && n >= (i == 0 ? 6 : 10) * cus) return 32 * 32 + 1 + i;
+    return (n > cus ? 112 * 112 : b.uniform && n >= cus / 8 ? 128 * 128 : 160 * 160) + 1 + i;
+}
+
+// The automatic choice never takes variant v for a batch of this size: one of
 // smaller key holds everything that v holds.
-static bool superseded(blp_handle h, int v, int64_t count, bool limited) {
+static bool superseded(blp_handle h, int v, const BatchSize& b, bool limited) {
     for (int w = 0; w < h->nreg; ++w)
-        if (w != v && usable(h, w, limited) && variant_key(h, w, count) < variant_key(h, v, count) &&
+        if (w != v && usable(h, w, limited) && variant_key(h, w, b) < variant_key(h, v, b) &&
             !h->variants[w].type1_only && h->variants[w].lps_per_block == 1 && can_replace(h, w, v))
             return true;
     return false;
@@ -281,15 +313,15 @@ static int64_t auto_min_count(blp_handle h, int v) {
 }
 
 // The variant that the automatic choice gives an LP of m rows, n columns and
-// nart artificial rows in a batch of `count` LPs, before any remap; -1: none
+// nart artificial rows in a batch of that size, before any remap; -1: none
 // holds it.
-static int best_variant(blp_handle h, int m, int n, int nart, int64_t count, bool limited) {
+static int best_variant(blp_handle h, int m, int n, int nart, const BatchSize& b, bool limited) {
     const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
     int best = -1;
     for (int v = 0; v < h->nreg; ++v)
         if (usable(h, v, limited) && holds(h->variants[v], m, n, nart) && (t1 || !h->variants[v].type1_only) &&
-            count >= auto_min_count(h, v) &&
-            (best < 0 || variant_key(h, v, count) < variant_key(h, best, count)))
+            b.count >= auto_min_count(h, v) &&
+            (best < 0 || variant_key(h, v, b) < variant_key(h, best, b)))
             best = v;
     return best;
 }
@@ -565,11 +597,6 @@ struct PendPlan {
     int max_occ = 1;        // and for any number of LPs (workspaces: a smaller batch may run more per CU)
     size_t lds = 0;         // dynamic LDS of a workgroup, bytes
 };
-// Most workgroups per CU of tile i: three (eight waves: two) waves per SIMD.
-static int pend_per_cu(blp_handle h, int i) {
-    const int most = std::max(1, 4 * kPendTiles[i].wpe / kPendTiles[i].waves);
-    return h->opt.workers_per_cu > 0 ? std::min(most, (int)h->opt.workers_per_cu) : most;
-}
 static PendPlan pend_plan(blp_handle h, int64_t lps, int m, int cols, bool alone, int tile = 0) {
     PendPlan p;
     p.tile = tile;
@@ -810,6 +837,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
 
     // Which register variants can receive an LP?  For a uniform simplex batch
     // only those chosen for some n_art in [0, m]; otherwise all.
+    const BatchSize size{K, uni, h->opt.mode};
     sp.maybe.assign(nreg, 0);
     if (h->opt.variant >= 0) {
         sp.maybe[h->opt.variant] = usable(h, h->opt.variant, limited) ? 1 : 0;
@@ -818,7 +846,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
             const int m = h->plan.m[0], n = h->plan.n[0];
             for (int nart = 0; nart <= m; ++nart) {
                 const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
-                const int best = best_variant(h, m, n, nart, K, limited);
+                const int best = best_variant(h, m, n, nart, size, limited);
                 if (best >= 0) {
                     const int r = h->remap[best];
                     const int to =
@@ -828,7 +856,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
             }
         } else {
             for (int v = 0; v < nreg; ++v) {
-                if (!usable(h, v, limited) || superseded(h, v, K, limited)) continue;
+                if (!usable(h, v, limited) || superseded(h, v, size, limited)) continue;
                 sp.maybe[v] = 1;
                 const int r = h->remap[v];
                 if (r < nreg && usable(h, r, limited)) sp.maybe[r] = 1;
@@ -869,7 +897,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         int one = -1;  // the variant for every number of artificial rows so far
         bool same = true;
         for (int nart = 0; same && nart <= m; ++nart) {
-            const int best = best_variant(h, m, n, nart, K, limited);
+            const int best = best_variant(h, m, n, nart, size, limited);
             if (nart == 0) one = best;
             same = best >= 0 && best == one && h->remap[best] == best;
         }
@@ -955,17 +983,17 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
     return BLP_SUCCESS;
 }
 
-static VariantTable variant_table(blp_handle h, int64_t count, bool limited) {
+static VariantTable variant_table(blp_handle h, const BatchSize& size, bool limited) {
     VariantTable vt{};
     vt.nreg = h->nreg;
-    vt.count = count;
+    vt.count = size.count;
     vt.force = h->opt.variant;
     for (int v = 0; v < h->nreg && v < kMaxVariants; ++v) {
         vt.rows[v] = usable(h, v, limited) ? h->variants[v].max_rows : 0;  // 0: never fits
         vt.cols[v] = h->variants[v].max_cols;
         vt.remap[v] = h->remap[v];
         vt.type1[v] = h->variants[v].type1_only;
-        vt.key[v] = variant_key(h, v, count);
+        vt.key[v] = variant_key(h, v, size);
         vt.sum[v] = h->variants[v].max_sum;
         vt.min_count[v] = auto_min_count(h, v);
     }
@@ -983,7 +1011,7 @@ static blp_error enqueue_binning(blp_handle h, SolvePlan& sp, hipStream_t s) {
     // zero the counters and the striped bin counters (bin_off is rewritten)
     int32_t* stripes = bin_count + stripes_at(nbins, sp.P.head_shards);
     HIP_TRY(h, launch_reset(bin_count, (int)counter_ints(nbins, sp.P.head_shards), s));
-    HIP_TRY(h, launch_classify(sp.P, variant_table(h, sp.P.count, sp.limited), sp.binid, stripes, s));
+    HIP_TRY(h, launch_classify(sp.P, variant_table(h, {sp.P.count, sp.uni, h->opt.mode}, sp.limited), sp.binid, stripes, s));
     HIP_TRY(h, launch_bin_offsets(stripes, bin_count, const_cast<int32_t*>(sp.P.bin_off), nbins, s));
     HIP_TRY(h, launch_scatter(sp.P.count, nbins, sp.binid, sp.P.bin_off, bin_fill, sp.list, s));
     // a uniform batch has one cost per bin; otherwise the kernels pop the
@@ -1037,6 +1065,7 @@ static std::vector<double> class_times(blp_handle h, const SolvePlan& sp) {
     const int nreg = h->nreg;
     const int64_t K = sp.P.count;
     std::vector<double> longest(nreg + 1, 0.0), sum(nreg + 1, 0.0);
+    const BatchSize size{K, sp.uni, h->opt.mode};
     constexpr int kSample = 48;
     const int ns = (int)std::min<int64_t>(K, kSample);
     for (int q = 0; q <= ns; ++q) {
@@ -1045,7 +1074,7 @@ static std::vector<double> class_times(blp_handle h, const SolvePlan& sp) {
         const int m = h->plan.m[k], n = h->plan.n[k];
         const double us = (0.045 * m * n + std::min(m, n)) * std::min(4.5, 1.0 + (m + n) / 80.0);
         for (int nart : {0, m / 2}) {
-            int v = h->opt.variant >= 0 ? h->opt.variant : h->opt.variant == -1 ? best_variant(h, m, n, nart, K, sp.limited) : -1;
+            int v = h->opt.variant >= 0 ? h->opt.variant : h->opt.variant == -1 ? best_variant(h, m, n, nart, size, sp.limited) : -1;
             if (v >= 0 && !holds(h->variants[v], m, n, nart)) v = -1;
             if (v >= 0 && h->opt.variant == -1) v = h->remap[v];
             if (v < 0 || v > nreg) v = nreg;
@@ -1076,12 +1105,14 @@ static std::vector<double> class_times(blp_handle h, const SolvePlan& sp) {
 // has to be worth more.  With fewer than 2,048 LPs a launch is as long as its
 // longest LP, which class_times overrates up to eightfold where no LP has two
 // phases: 500 one-phase LPs of 20..60 160 us one after another, 220 forked, 400
-// of both kinds of 5..110 3.6 ms and 2.3.  With more the sums count as well:
-// 2,100 of 4..12 204 us and 235, 4,000 of 5..110 3.9 ms and 2.9.
+// of both kinds of 5..110 3.6 ms and 2.3, 128 of 60..120 5.8 ms and 2.8 (one-
+// phase 257 us and 229), 33 one-phase ones of 5..110 213 us and 228.  With more
+// the sums count as well: 2,100 of 4..12 204 us and 235, 4,000 of 5..110 3.9 ms
+// and 2.9.
 // A uniform batch has one dominant class.  A captured sequence (graph mode)
 // keeps every class on the capturing stream; while the caller captures s,
 // batches fork from kForkManyLps LPs.
-static constexpr int64_t kForkMinLps = 256, kForkManyLps = 2048;
+static constexpr int64_t kForkMinLps = 32, kForkManyLps = 2048;
 static constexpr double kForkMinUs = 1000.0, kForkManyUs = 250.0;  // class_times beside the longest
 static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, bool capturing = false) {
     const int nreg = h->nreg;
@@ -1774,7 +1805,7 @@ blp_error blp_solve_shared(blp_handle h, int32_t m, int32_t n, const double* A, 
     rt.cold = -1;
     for (int v = 0; v < nreg && h->opt.layout == BLP_LAYOUT_COLUMN && h->opt.mem_limit == 0; ++v)
         if (rt.cold < 0 && h->variants[v].pend >= 0 && holds(h->variants[v], m, n, m) &&
-            variant_key(h, v, count) < 112 * 112)
+            variant_key(h, v, {count, true, BLP_MODE_PERSISTENT}) < 112 * 112)
             rt.cold = v;
     rt.tile_rows = rows;
     rt.tile_cols = cols;

@@ -2283,17 +2283,29 @@ blp_error blp_autotune(blp_handle h, const blp_batch* B, int32_t sample, const c
         }
         saved[v] = best;
     }
-    // the streaming kernel's loads in flight per lane (8 or 32), timed on a
-    // sample of the streaming bin, each depth with its own occupancy-sized
-    // grid (never more workgroups than the workspace has slots)
+    // The loads in flight per lane (8 or 32) of the kernel that streams at every
+    // pivot, timed on a sample of the LPs that it gets, each depth with its own
+    // occupancy-sized grid (never more workgroups than the workspace has slots).
+    // The pending-pivot kernel, which takes the other streamed LPs, has no such
+    // choice; where it takes all of them the depth is the untuned one.
     int deep = saved_deep;
+    std::vector<int32_t> own((size_t)cnt[nreg]);
     if (cnt[nreg] > 0) {
-        const int S = std::min<int>(sample, cnt[nreg]);
+        HIP_TRY(h, hipMemcpyAsync(own.data(), sp.list + off[nreg], sizeof(int32_t) * own.size(), hipMemcpyDeviceToHost, s));
+        HIP_TRY(h, hipStreamSynchronize(s));
+        const auto pends = [&](int32_t k) {
+            return h->opt.layout == BLP_LAYOUT_COLUMN && pend_shape(h->plan.m[sp.uni ? 0 : k], h->plan.n[sp.uni ? 0 : k]);
+        };
+        own.erase(std::remove_if(own.begin(), own.end(), pends), own.end());
+        if (own.empty()) deep = sp.gm_deep ? 1 : 0;
+    }
+    if (!own.empty()) {
+        const int S = (int)std::min<size_t>((size_t)sample, own.size());
         HIP_TRY(h, h->tune.reserve(sizeof(int32_t) * (kList + (size_t)S)));
         int32_t* tb = h->tune.as<int32_t>();
         int32_t hdr[2] = {0, S};
         HIP_TRY(h, hipMemcpyAsync(tb, hdr, sizeof hdr, hipMemcpyHostToDevice, s));
-        HIP_TRY(h, hipMemcpyAsync(tb + kList, sp.list + off[nreg], sizeof(int32_t) * S, hipMemcpyDeviceToDevice, s));
+        HIP_TRY(h, hipMemcpyAsync(tb + kList, own.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, s));
         KParams Q = sp.P;
         Q.list = tb + kList;
         Q.bin_off = tb;

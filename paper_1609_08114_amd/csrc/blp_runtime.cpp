@@ -293,12 +293,24 @@ static int variant_key(blp_handle h, int v, const BatchSize& b) {
     return (n > cus ? 112 * 112 : b.uniform && n >= cus / 8 ? 128 * 128 : 160 * 160) + 1 + i;
 }
 
-// The automatic choice never takes variant v for a batch of this size: one of
-// smaller key holds everything that v holds.
-static bool superseded(blp_handle h, int v, const BatchSize& b, bool limited) {
+// All variants' keys for a batch.
+struct Keys {
+    int64_t count;
+    int of[kMaxVariants];
+};
+static Keys variant_keys(blp_handle h, const BatchSize& b) {
+    Keys k;
+    k.count = b.count;
+    for (int v = 0; v < h->nreg; ++v) k.of[v] = variant_key(h, v, b);
+    return k;
+}
+
+// The automatic choice never takes variant v for this batch: one of smaller
+// key holds everything that v holds.
+static bool superseded(blp_handle h, int v, const Keys& keys, bool limited) {
     for (int w = 0; w < h->nreg; ++w)
-        if (w != v && usable(h, w, limited) && variant_key(h, w, b) < variant_key(h, v, b) &&
-            !h->variants[w].type1_only && h->variants[w].lps_per_block == 1 && can_replace(h, w, v))
+        if (w != v && usable(h, w, limited) && keys.of[w] < keys.of[v] && !h->variants[w].type1_only &&
+            h->variants[w].lps_per_block == 1 && can_replace(h, w, v))
             return true;
     return false;
 }
@@ -313,15 +325,13 @@ static int64_t auto_min_count(blp_handle h, int v) {
 }
 
 // The variant that the automatic choice gives an LP of m rows, n columns and
-// nart artificial rows in a batch of that size, before any remap; -1: none
-// holds it.
-static int best_variant(blp_handle h, int m, int n, int nart, const BatchSize& b, bool limited) {
+// nart artificial rows in this batch, before any remap; -1: none holds it.
+static int best_variant(blp_handle h, int m, int n, int nart, const Keys& keys, bool limited) {
     const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
     int best = -1;
     for (int v = 0; v < h->nreg; ++v)
-        if (usable(h, v, limited) && holds(h->variants[v], m, n, nart) && (t1 || !h->variants[v].type1_only) &&
-            b.count >= auto_min_count(h, v) &&
-            (best < 0 || variant_key(h, v, b) < variant_key(h, best, b)))
+        if ((best < 0 || keys.of[v] < keys.of[best]) && holds(h->variants[v], m, n, nart) && usable(h, v, limited) &&
+            (t1 || !h->variants[v].type1_only) && keys.count >= auto_min_count(h, v))
             best = v;
     return best;
 }
@@ -837,16 +847,21 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
 
     // Which register variants can receive an LP?  For a uniform simplex batch
     // only those chosen for some n_art in [0, m]; otherwise all.
-    const BatchSize size{K, uni, h->opt.mode};
+    const Keys keys = variant_keys(h, {K, uni, h->opt.mode});
+    std::vector<int> best_of;  // uniform batch: the automatic choice by number of artificial rows
+    if (uni && any_simplex && h->opt.variant == -1) {
+        best_of.reserve((size_t)max_m + 1);
+        for (int nart = 0; nart <= max_m; ++nart)
+            best_of.push_back(best_variant(h, max_m, pl.n[0], nart, keys, limited));
+    }
     sp.maybe.assign(nreg, 0);
     if (h->opt.variant >= 0) {
         sp.maybe[h->opt.variant] = usable(h, h->opt.variant, limited) ? 1 : 0;
     } else if (h->opt.variant == -1 && any_simplex) {
         if (uni) {
-            const int m = h->plan.m[0], n = h->plan.n[0];
-            for (int nart = 0; nart <= m; ++nart) {
+            for (int nart = 0; nart <= max_m; ++nart) {
                 const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
-                const int best = best_variant(h, m, n, nart, size, limited);
+                const int best = best_of[nart];
                 if (best >= 0) {
                     const int r = h->remap[best];
                     const int to =
@@ -856,7 +871,7 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
             }
         } else {
             for (int v = 0; v < nreg; ++v) {
-                if (!usable(h, v, limited) || superseded(h, v, size, limited)) continue;
+                if (!usable(h, v, limited) || superseded(h, v, keys, limited)) continue;
                 sp.maybe[v] = 1;
                 const int r = h->remap[v];
                 if (r < nreg && usable(h, r, limited)) sp.maybe[r] = 1;
@@ -893,14 +908,9 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
     // the LPs from the queue in their order (20,000 LPs 30 x 30: 207 us with the
     // binning, 178 without).
     if (may_direct && sp.direct_v < 0) {
-        const int m = h->plan.m[0], n = h->plan.n[0];
-        int one = -1;  // the variant for every number of artificial rows so far
-        bool same = true;
-        for (int nart = 0; same && nart <= m; ++nart) {
-            const int best = best_variant(h, m, n, nart, size, limited);
-            if (nart == 0) one = best;
-            same = best >= 0 && best == one && h->remap[best] == best;
-        }
+        const int one = best_of[0];  // for every number of artificial rows
+        const bool same = one >= 0 && h->remap[one] == one &&
+                          std::all_of(best_of.begin(), best_of.end(), [&](int v) { return v == one; });
         if (same) {
             sp.direct_v = one;
             sp.direct_queue = true;
@@ -1065,7 +1075,7 @@ static std::vector<double> class_times(blp_handle h, const SolvePlan& sp) {
     const int nreg = h->nreg;
     const int64_t K = sp.P.count;
     std::vector<double> longest(nreg + 1, 0.0), sum(nreg + 1, 0.0);
-    const BatchSize size{K, sp.uni, h->opt.mode};
+    const Keys keys = variant_keys(h, {K, sp.uni, h->opt.mode});
     constexpr int kSample = 48;
     const int ns = (int)std::min<int64_t>(K, kSample);
     for (int q = 0; q <= ns; ++q) {
@@ -1074,7 +1084,7 @@ static std::vector<double> class_times(blp_handle h, const SolvePlan& sp) {
         const int m = h->plan.m[k], n = h->plan.n[k];
         const double us = (0.045 * m * n + std::min(m, n)) * std::min(4.5, 1.0 + (m + n) / 80.0);
         for (int nart : {0, m / 2}) {
-            int v = h->opt.variant >= 0 ? h->opt.variant : h->opt.variant == -1 ? best_variant(h, m, n, nart, size, sp.limited) : -1;
+            int v = h->opt.variant >= 0 ? h->opt.variant : h->opt.variant == -1 ? best_variant(h, m, n, nart, keys, sp.limited) : -1;
             if (v >= 0 && !holds(h->variants[v], m, n, nart)) v = -1;
             if (v >= 0 && h->opt.variant == -1) v = h->remap[v];
             if (v < 0 || v > nreg) v = nreg;

@@ -142,12 +142,13 @@ struct PendTile {
     constexpr int slots() const { return waves * 128; }
 };
 // One wave holds LPs of up to 64 rows without a barrier; 128 rows take two
-// waves rather than one with two rows per lane (10.4 against 13.0 ms on 4,000
-// two-phase LPs 100 x 100: the flush needs the waves), 256 four, 512 eight.
+// waves rather than one with two rows per lane (in an earlier version of the
+// kernel 10.4 against 13.0 ms on 4,000 two-phase LPs 100 x 100: the flush needs
+// the waves), 256 four, 512 eight.
 // Three waves per SIMD up to four waves: with 128 registers for four, 4,000 of
-// 100 x 100 take 8.2 ms against 7.9, 50,000 one-phase ones 2.84 against 2.41.
+// 100 x 100 take 8.4 ms against 8.0, 50,000 one-phase ones 2.88 against 2.35.
 // Eight waves: one LP per CU (two take as long), and the registers for it: a
-// mixed batch of 2,000 LPs of up to 300 x 300 20.3 ms, with 128 registers 23.3.
+// mixed batch of 2,000 LPs of up to 300 x 300 21.6 ms, with 128 registers 23.6.
 constexpr PendTile kPendTiles[] = {{1, 4, 12, 3}, {2, 4, 8, 3}, {4, 4, 16, 3}, {8, 4, 24, 2}};
 constexpr int kPendTileCount = (int)(sizeof(kPendTiles) / sizeof(kPendTiles[0]));
 hipError_t launch_pend(const KParams& P, int tile, int grid, size_t lds_bytes, hipStream_t s);

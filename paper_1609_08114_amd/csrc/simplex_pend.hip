@@ -26,8 +26,9 @@
 //
 // Pivot (l, e) at pending index s: row l becomes the pivot row p, so its older
 // pending factors count for nothing and its factor is 1 on an entry of 0
-// (fma(1, p, 0) = p); slot e becomes the leaving variable's column, on an
-// entry of 0 likewise.  A bit per row and slot (`rb`, `sb`) says that its
+// (fma(1, p, 0) = p; a -0 becomes +0, as in the kernels that update at every
+// pivot); slot e becomes the leaving variable's column, on an entry of 0
+// likewise.  A bit per row and slot (`rb`, `sb`) says that its
 // tableau entries count as 0, and its older factors are zeroed, which changes
 // nothing while the other factor is finite: a pivot with a non-finite entry is
 // flushed before the next one, so that all older terms are finite.

@@ -305,16 +305,6 @@ static Keys variant_keys(blp_handle h, const BatchSize& b) {
     return k;
 }
 
-// The automatic choice never takes variant v for this batch: one of smaller
-// key holds everything that v holds.
-static bool superseded(blp_handle h, int v, const Keys& keys, bool limited) {
-    for (int w = 0; w < h->nreg; ++w)
-        if (w != v && usable(h, w, limited) && keys.of[w] < keys.of[v] && !h->variants[w].type1_only &&
-            h->variants[w].lps_per_block == 1 && can_replace(h, w, v))
-            return true;
-    return false;
-}
-
 // Smallest batch for which the automatic choice may use variant v: a variant
 // that packs several LPs into a workgroup (the lane kernel, 64 per wave)
 // needs a quarter of its workgroups per CU to beat one LP per wave; smaller
@@ -322,6 +312,17 @@ static bool superseded(blp_handle h, int v, const Keys& keys, bool limited) {
 static int64_t auto_min_count(blp_handle h, int v) {
     const int64_t per = h->variants[v].lps_per_block;
     return per > 1 ? per * h->cu_count / 4 : 0;
+}
+
+// The automatic choice never takes variant v for this batch: it needs more
+// LPs, or one that comes before it holds everything that it holds.
+static bool superseded(blp_handle h, int v, const Keys& keys, bool limited) {
+    if (keys.count < auto_min_count(h, v)) return true;
+    for (int w = 0; w < h->nreg; ++w)
+        if (w != v && usable(h, w, limited) && (keys.of[w] < keys.of[v] || (keys.of[w] == keys.of[v] && w < v)) &&
+            keys.count >= auto_min_count(h, w) && !h->variants[w].type1_only && can_replace(h, w, v))
+            return true;
+    return false;
 }
 
 // The variant that the automatic choice gives an LP of m rows, n columns and
@@ -845,39 +846,6 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
         }
     }
 
-    // Which register variants can receive an LP?  For a uniform simplex batch
-    // only those chosen for some n_art in [0, m]; otherwise all.
-    const Keys keys = variant_keys(h, {K, uni, h->opt.mode});
-    std::vector<int> best_of;  // uniform batch: the automatic choice by number of artificial rows
-    if (uni && any_simplex && h->opt.variant == -1) {
-        best_of.reserve((size_t)max_m + 1);
-        for (int nart = 0; nart <= max_m; ++nart)
-            best_of.push_back(best_variant(h, max_m, pl.n[0], nart, keys, limited));
-    }
-    sp.maybe.assign(nreg, 0);
-    if (h->opt.variant >= 0) {
-        sp.maybe[h->opt.variant] = usable(h, h->opt.variant, limited) ? 1 : 0;
-    } else if (h->opt.variant == -1 && any_simplex) {
-        if (uni) {
-            for (int nart = 0; nart <= max_m; ++nart) {
-                const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
-                const int best = best_of[nart];
-                if (best >= 0) {
-                    const int r = h->remap[best];
-                    const int to =
-                        r >= nreg || (usable(h, r, limited) && (t1 || !h->variants[r].type1_only)) ? r : best;
-                    if (to < nreg) sp.maybe[to] = 1;
-                }
-            }
-        } else {
-            for (int v = 0; v < nreg; ++v) {
-                if (!usable(h, v, limited) || superseded(h, v, keys, limited)) continue;
-                sp.maybe[v] = 1;
-                const int r = h->remap[v];
-                if (r < nreg && usable(h, r, limited)) sp.maybe[r] = 1;
-            }
-        }
-    }
     // A uniform batch small enough that every LP gets a place of its own at
     // once (a workgroup, or a lane of the lane kernel once the batch is large
     // enough for it), with a register variant that holds the shape whatever
@@ -900,6 +868,41 @@ static blp_error prepare(blp_handle h, const blp_batch* B, const blp_outputs* ou
                     barea = a;
                     sp.direct_v = v;
                 }
+            }
+        }
+    }
+    // Which register variants can receive an LP?  For a uniform simplex batch
+    // only those chosen for some n_art in [0, m]; otherwise all.
+    const Keys keys = variant_keys(h, {K, uni, h->opt.mode});
+    std::vector<int> best_of;  // uniform batch: the automatic choice by number of artificial rows
+    if (uni && any_simplex && h->opt.variant == -1 && sp.direct_v < 0) {
+        best_of.reserve((size_t)max_m + 1);
+        for (int nart = 0; nart <= max_m; ++nart)
+            best_of.push_back(best_variant(h, max_m, pl.n[0], nart, keys, limited));
+    }
+    sp.maybe.assign(nreg, 0);
+    if (h->opt.variant >= 0) {
+        sp.maybe[h->opt.variant] = usable(h, h->opt.variant, limited) ? 1 : 0;
+    } else if (h->opt.variant == -1 && any_simplex) {
+        if (sp.direct_v >= 0) {
+            sp.maybe[sp.direct_v] = 1;
+        } else if (uni) {
+            for (int nart = 0; nart <= max_m; ++nart) {
+                const bool t1 = nart == 0 && h->opt.pivot_rule == BLP_RULE_LPC;
+                const int best = best_of[nart];
+                if (best >= 0) {
+                    const int r = h->remap[best];
+                    const int to =
+                        r >= nreg || (usable(h, r, limited) && (t1 || !h->variants[r].type1_only)) ? r : best;
+                    if (to < nreg) sp.maybe[to] = 1;
+                }
+            }
+        } else {
+            for (int v = 0; v < nreg; ++v) {
+                if (!usable(h, v, limited) || superseded(h, v, keys, limited)) continue;
+                sp.maybe[v] = 1;
+                const int r = h->remap[v];
+                if (r < nreg && usable(h, r, limited)) sp.maybe[r] = 1;
             }
         }
     }
@@ -1066,11 +1069,14 @@ static hipError_t launch_variant(blp_handle h, const SolvePlan& sp, int v, const
     return launch_pend(Q, c.plan.tile, (int)std::min<int64_t>(grid, c.workers), c.plan.lds, s);
 }
 
+// Rough time of an LP, in us: pivots of the two-phase LPs of the workloads, 1 to
+// 4.5 us each.
+static double lp_time(int m, int n) { return (0.045 * m * n + std::min(m, n)) * std::min(4.5, 1.0 + (m + n) / 80.0); }
+
 // Rough time of each class's launch over a mixed batch, in us (0: probably no
 // LPs): the longest LP of a sample of the batch, or its workgroups' share of
 // all of them.  The number of artificial rows is not known here (0 and half
-// of the rows are assumed, once each), nor whether an LP takes two phases:
-// pivots are those of two-phase LPs of the workloads, 1 to 4.5 us each.
+// of the rows are assumed, once each), nor whether an LP takes two phases.
 static std::vector<double> class_times(blp_handle h, const SolvePlan& sp) {
     const int nreg = h->nreg;
     const int64_t K = sp.P.count;
@@ -1082,7 +1088,7 @@ static std::vector<double> class_times(blp_handle h, const SolvePlan& sp) {
         const int64_t k = q < ns ? (2 * q + 1) * K / (2 * ns) : h->plan.largest;
         if (k < 0 || h->plan.kind[k] != 0) continue;
         const int m = h->plan.m[k], n = h->plan.n[k];
-        const double us = (0.045 * m * n + std::min(m, n)) * std::min(4.5, 1.0 + (m + n) / 80.0);
+        const double us = lp_time(m, n);
         for (int nart : {0, m / 2}) {
             int v = h->opt.variant >= 0 ? h->opt.variant : h->opt.variant == -1 ? best_variant(h, m, n, nart, keys, sp.limited) : -1;
             if (v >= 0 && !holds(h->variants[v], m, n, nart)) v = -1;
@@ -1145,11 +1151,14 @@ static blp_error enqueue_persistent(blp_handle h, SolvePlan& sp, hipStream_t s, 
     std::vector<double> us(nreg + 1, 0.0);  // by class
     std::vector<int> on(nc, 0);
     int nf = 0;  // forks used
+    const double least = K < kForkManyLps ? kForkMinUs : kForkManyUs;
+    // (first a bound: every launch as long as the largest LP and its share of a CU each)
+    if (forked && lp_time(h->plan.max_m, h->plan.max_n) * nc * (1.0 + (double)K / h->cu_count) < least) forked = false;
     if (forked) {
         us = class_times(h, sp);
         std::vector<double> launch(nc);
         for (int i = 0; i < nc; ++i) launch[i] = us[cls[i]];
-        nf = plan_forks(launch, blp_handle_s::kForks, K < kForkManyLps ? kForkMinUs : kForkManyUs, on);
+        nf = plan_forks(launch, blp_handle_s::kForks, least, on);
         forked = nf > 0;
     }
     // a launch lasts at least as long as its largest LP, and the smaller classes
